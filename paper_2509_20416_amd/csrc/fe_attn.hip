@@ -470,6 +470,392 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
   op[1] = Elt<T>::from_f(ay / L);
 }
 
+// ---- tiles of query rows (bf16 multi-position prefill) ---------------------------
+// The rows of a prefill share their sequence's cache rows: row m sees
+// keys start .. start + P_m - 1.  Done row by row (k_attn_mma) every row
+// streams its own prefix through LDS, so a 1024-row prompt reads its keys 512
+// times over and each MFMA carries GH live columns of 16.  Here a workgroup
+// takes a tile of up to kTileQ / GH consecutive rows with one start and the GH
+// heads of a head group, i.e. kTileQ (row, head) columns, streams the union
+// of their keys once, and masks each column's scores past its own P.
+//
+// Four waves of 16 columns, one per SIMD, stages of 32 keys in a four-slot
+// ring (64 KB at D = 128: two workgroups per CU, which hide each other's
+// latencies).  The arithmetic is k_attn_mma's: q split into a bf16 high and
+// low part, lazily raised maxima, probabilities as bf16 whose sum (a product
+// with ones) adds the same rounded values; the row's own key (fp32) joins at
+// the end, unrotated, since rotating it and the query by the same position
+// leaves their product unchanged.
+// Bound by the chain read - score - maximum - exponential - product of a
+// stage, not by bytes: 1024 rows at the 8B shapes (32 query, 8 KV heads, D 128)
+// take 41 us per layer, against 315 us for the row-by-row launches and their
+// merges; tiles of 128 columns took 52 us with four waves (two column tiles
+// each) and 46 us with eight, because a prompt's last tile sees twice the
+// average keys and only two small workgroups per CU even that out.
+constexpr int kTileQ = 64, kTileWaves = 4;
+
+// The tiles: tiles[0] their number, tile i rows tiles[1 + i] .. tiles[2 + i] - 1.
+// A tile is at most tq consecutive rows of one run: rows with the same
+// start whose ranges are valid (an invalid row is a tile of its own).  One
+// workgroup; two scans (the run's first row, the tile's index) per 1024 rows.
+__global__ __launch_bounds__(1024) void k_attn_tile_plan(const int32_t *__restrict__ ranges, int M,
+                                                         int pmax, int tq,
+                                                         int32_t *__restrict__ tiles) {
+  __shared__ int s_w[16], s_carry[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto bad = [&](int m) {
+    const int P = ranges[2 * m + 1] - ranges[2 * m];
+    return P < 0 || P > pmax;
+  };
+  if (tid == 0) s_carry[0] = s_carry[1] = 0;
+  __syncthreads();
+  for (int m0 = 0; m0 < M; m0 += 1024) {
+    const int m = m0 + tid;
+    bool first = m < M;
+    if (m > 0 && m < M) first = bad(m) || bad(m - 1) || ranges[2 * m] != ranges[2 * m - 2];
+    // the run's first row: the largest row <= m that starts one
+    int x = first ? m : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x = max(x, y);
+    }
+    if (lane == 63) s_w[wave] = x;
+    __syncthreads();
+    x = max(x, s_carry[0]);
+    for (int w = 0; w < wave; ++w) x = max(x, s_w[w]);
+    __syncthreads();
+    const bool head = m < M && (m - x) % tq == 0;
+    const uint64_t vote = __ballot(head);
+    if (lane == 63) s_w[wave] = __popcll(vote);
+    __syncthreads();
+    int idx = s_carry[1] + __popcll(vote & ((1ull << lane) - 1));
+    int total = 0;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) idx += s_w[w];
+      total += s_w[w];
+    }
+    if (head) tiles[1 + idx] = m;
+    __syncthreads();
+    if (tid == 1023) s_carry[0] = x;
+    if (tid == 0) s_carry[1] += total;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    tiles[0] = s_carry[1];
+    tiles[1 + s_carry[1]] = M;
+  }
+}
+
+template <int D, int GH>
+__global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *__restrict__ Kc,
+                                                      const bf16_t *__restrict__ Vc,
+                                                      const int32_t *__restrict__ ranges,
+                                                      const int32_t *__restrict__ tiles,
+                                                      const float *__restrict__ q,
+                                                      const float *__restrict__ knew,
+                                                      const float *__restrict__ vnew,
+                                                      bf16_t *__restrict__ out, int Hq, int Hkv,
+                                                      const float *__restrict__ rope, int pmax) {
+  constexpr int NKC = D / 32, NDT = D / 16, VPR = D / 8, RB = 2 * D, HD = D / 2;
+  constexpr int RPW = 256 / RB, LQ = VPR == 16 ? 3 : 2;
+  constexpr int SK = 32, HALF = SK * RB, STAGE = 2 * HALF, S = 4;
+  constexpr int NL = STAGE / 1024 / kTileWaves;  // 1 KB loads per wave per stage
+  constexpr int CT = kTileQ / 16 / kTileWaves;   // 16-column tiles per wave
+  static_assert((S - 1) * NL <= 63, "outstanding loads stay within the vmcnt range");
+  __shared__ __attribute__((aligned(16))) unsigned char ring[S][STAGE];
+  __shared__ int s_p[kTileWaves];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int G = Hq / Hkv, ngrp = G / GH, ncols = Hkv * ngrp;
+  const size_t rs = (size_t)Hkv * D;
+  const float qscale = 1.4426950408889634f * rsqrtf((float)D);
+  // 16-byte piece p of row R sits at p ^ swzk(R) (K) or p ^ swz(R) (V, as in
+  // attn_unit), rows mod 16.  A 16-byte read is served to lanes 0-3, 12-15 and
+  // 20-27 together, then 4-11, 16-19 and 28-31, and so on: under swzk those
+  // sixteen (row, piece) pairs of a K operand lie in distinct banks, under swz
+  // they met in pairs.
+  auto swz = [](int R) {
+    const int Q = (R & 15) / RPW;
+    return (2 * Q + (Q >> LQ)) & (VPR - 1);
+  };
+  auto swzk = [](int R) { return (R / RPW) & (VPR - 1); };
+  // this lane's row and element offset in each of its loads (a stage's K rows,
+  // then its V rows)
+  int lrow[NL], loff[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int o = (j * kTileWaves + wave) * 1024 + 16 * lane, R = (o % HALF) / RB, sl = (o % RB) / 16;
+    lrow[j] = R;
+    loff[j] = 8 * (sl ^ (o < HALF ? swzk(R) : swz(R)));
+  }
+  // byte offsets of this lane's operand reads in a stage: 16-byte piece 4kc + g
+  // of K row r (kc: ^ 64 kc), 8 bytes of V row 4g + r / 4 (dim tile dt: ^ 32 dt);
+  // the second 16 rows lie 16 RB further (the swizzle repeats)
+  const int koff = r * RB + 16 * (g ^ swzk(r));
+  const int voff = HALF + (4 * g + (r >> 2)) * RB + 16 * (((r & 3) >> 1) ^ swz(4 * g + (r >> 2))) + 8 * (r & 1);
+  const uint32_t ring0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)&ring[0][0]) + wave * 1024);
+  const int nitems = tiles[0] * ncols;
+  // The last tiles of a prompt see the most keys and go first; the second
+  // half of the grid, which shares the compute units of the first, takes its
+  // items in the opposite order, so a unit gets a long item and a short one.
+  const int half = gridDim.x / 2, wg = blockIdx.x;
+  const int first = wg < half ? wg : (int)gridDim.x - 1 - (wg - half);
+  for (int it = first; it < nitems; it += gridDim.x) {
+    const int t = tiles[0] - 1 - it / ncols, col = it % ncols;
+    const int row0 = tiles[1 + t], n = tiles[2 + t] - row0;
+    const int c = col / ngrp, h0 = c * G + (col % ngrp) * GH;
+    const int start = ranges[2 * row0];
+    // column 16 i + r of this wave: row mrow[i], head mh[i], its prefix length
+    int mrow[CT], mh[CT], P[CT];
+    bool bad[CT], live[CT];
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const int cidx = wave * 16 * CT + 16 * i + r;
+      live[i] = cidx / GH < n;
+      mrow[i] = row0 + min(cidx / GH, n - 1);
+      mh[i] = h0 + cidx % GH;
+      P[i] = attn_prefix(Seqs{ranges, 1}, mrow[i], pmax, bad[i]);
+    }
+    int pmx = P[0], pmn = P[0];
+#pragma unroll
+    for (int i = 1; i < CT; ++i) {
+      pmx = max(pmx, P[i]);
+      pmn = min(pmn, P[i]);
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      pmx = max(pmx, __shfl_xor(pmx, o, 64));
+      pmn = min(pmn, __shfl_xor(pmn, o, 64));
+    }
+    pmx = __builtin_amdgcn_readfirstlane(pmx);  // this wave's columns: most and fewest keys
+    pmn = __builtin_amdgcn_readfirstlane(pmn);
+    __syncthreads();  // the ring and s_p of the last item are free
+    if (lane == 0) s_p[wave] = pmx;
+    __syncthreads();
+    int Pt = s_p[0];  // keys of the tile
+#pragma unroll
+    for (int w = 1; w < kTileWaves; ++w) Pt = max(Pt, s_p[w]);
+    const int nst = (Pt + SK - 1) / SK;
+    const bf16_t *kb = Kc + ((size_t)start * Hkv + c) * D, *vb = Vc + ((size_t)start * Hkv + c) * D;
+    // stage st (clamped: past the end the last one again, so every wave
+    // issues the same count), rows clamped inside the tile's keys
+    auto issue = [&](int st) {
+      const int k0 = min(st, nst - 1) * SK;
+      const uint32_t dst = ring0 + (st % S) * STAGE;
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const bf16_t *src = (j * kTileWaves + wave) * 1024 < HALF ? kb : vb;  // uniform
+        ring_dma16(src + (size_t)min(k0 + lrow[j], Pt - 1) * rs + loff[j], dst + j * (kTileWaves * 1024));
+      }
+    };
+    if (nst > 0)
+#pragma unroll
+      for (int st = 0; st < S - 1; ++st) issue(st);
+
+    // q as B operands (high and low bf16 parts, rotated at P and scaled), and
+    // the score of the row's own key, from the unrotated values
+    u32x4 qh[CT][NKC], ql[CT][NKC];
+    float sown[CT];
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const float *qp = q + ((size_t)mrow[i] * Hq + mh[i]) * D + 8 * g;
+      const float *kp = knew + ((size_t)mrow[i] * Hkv + c) * D + 8 * g;
+      float qf[NKC][8], dot = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc)
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const f32x4 a = *reinterpret_cast<const f32x4 *>(qp + 32 * kc + 4 * w);
+          const f32x4 b = *reinterpret_cast<const f32x4 *>(kp + 32 * kc + 4 * w);
+          qf[kc][4 * w] = a.x; qf[kc][4 * w + 1] = a.y; qf[kc][4 * w + 2] = a.z; qf[kc][4 * w + 3] = a.w;
+          dot += a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+        }
+      sown[i] = xor32_sum(xor16_sum(dot)) * qscale;
+#pragma unroll
+      for (int kc = 0; kc < NKC / 2; ++kc)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const f32x4 cw = *reinterpret_cast<const f32x4 *>(rope + ((size_t)P[i] * HD + 32 * kc + 8 * g) * 2 + 4 * w);
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int e = 2 * w + u;
+            const float cs = u ? cw.z : cw.x, sn = u ? cw.w : cw.y;
+            const float x1 = qf[kc][e], x2 = qf[kc + NKC / 2][e];
+            qf[kc][e] = x1 * cs - x2 * sn;
+            qf[kc + NKC / 2][e] = x2 * cs + x1 * sn;
+          }
+        }
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        uint32_t hw[4], lw[4];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const float a0 = qf[kc][e] * qscale, a1 = qf[kc][e + 1] * qscale;
+          hw[e / 2] = pack_bf16(a0, a1);
+          lw[e / 2] = pack_bf16(a0 - __uint_as_float(hw[e / 2] << 16),
+                                a1 - __uint_as_float(hw[e / 2] & 0xffff0000u));
+        }
+        qh[i][kc] = u32x4{hw[0], hw[1], hw[2], hw[3]};
+        ql[i][kc] = u32x4{lw[0], lw[1], lw[2], lw[3]};
+      }
+    }
+
+    // lacc: the probabilities' sums, as the product with a row of ones
+    float mx_[CT];
+    f32x4 oacc[CT][NDT], lacc[CT];
+    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      mx_[i] = -INFINITY;
+      lacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) oacc[i][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int st = 0; st < nst; ++st) {
+      // stage st has landed (this wave's part) and this wave's reads of the
+      // slot that is refilled next are done; the barrier extends both
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * NL, 0));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      issue(st + S - 1);
+      const int k0 = st * SK;
+      if (k0 >= pmx) continue;  // no column of this wave sees this stage
+      const unsigned char *ringp = &ring[0][0];
+      const int kst = (st % S) * STAGE + koff, vst = (st % S) * STAGE + voff;
+      f32x4 s[2][CT];  // [16-key half][column tile]
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < CT; ++i) s[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const u32x4 ka = *reinterpret_cast<const u32x4 *>(ringp + (kst ^ (64 * kc)) + 16 * h * RB);
+#pragma unroll
+          for (int i = 0; i < CT; ++i) {
+            s[h][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, ql[i][kc]), s[h][i], 0, 0, 0);
+            s[h][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qh[i][kc]), s[h][i], 0, 0, 0);
+          }
+        }
+      const bool masked = k0 + SK > pmn;  // some column sees only part of the stage
+      if (masked) {
+#pragma unroll
+        for (int i = 0; i < CT; ++i) {
+          const int left = P[i] - k0 - 4 * g;  // this lane's keys 16h + v below it are seen
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (16 * h + v >= left) s[h][i][v] = -INFINITY;
+        }
+      }
+      u32x4 pb[CT];  // lane (r, g): keys 4g + e of the first half, then of the second
+#pragma unroll
+      for (int i = 0; i < CT; ++i) {
+        float mx = fmaxf(fmaxf(fmaxf(s[0][i].x, s[0][i].y), fmaxf(s[0][i].z, s[0][i].w)),
+                         fmaxf(fmaxf(s[1][i].x, s[1][i].y), fmaxf(s[1][i].z, s[1][i].w)));
+        mx = xor32_max(xor16_max(mx));
+        const bool up = mx > mx_[i] + kLazyMax;
+        if (__builtin_amdgcn_ballot_w64(up)) {
+          const float mn = up ? mx : mx_[i];
+          const float alpha = sexp2(mx_[i], mn);
+          mx_[i] = mn;
+          lacc[i] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt) oacc[i][dt] *= alpha;
+        }
+        // a column that has seen no key yet has the maximum -inf: subtract 0
+        const float m = mx_[i] == -INFINITY ? 0.f : mx_[i];
+        auto p2 = [&](float a, float b) {
+          return pack_bf16(__builtin_amdgcn_exp2f(a - m), __builtin_amdgcn_exp2f(b - m));
+        };
+        pb[i] = u32x4{p2(s[0][i].x, s[0][i].y), p2(s[0][i].z, s[0][i].w),
+                      p2(s[1][i].x, s[1][i].y), p2(s[1][i].z, s[1][i].w)};
+        lacc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, ones), __builtin_bit_cast(bf16x8, pb[i]), lacc[i], 0, 0, 0);
+      }
+      if (masked) {
+        uint32_t odd = 0;  // a non-finite value in the stage's V rows
+#pragma unroll 2
+        for (int o = 16 * lane; o < HALF; o += 1024) {
+          const u32x4 w4 = *reinterpret_cast<const u32x4 *>(ringp + (st % S) * STAGE + HALF + o);
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const uint32_t x = w4[w];
+            odd |= (uint32_t)((x & 0x7f80u) == 0x7f80u) | (uint32_t)((x & 0x7f800000u) == 0x7f800000u);
+          }
+        }
+        if (__builtin_amdgcn_ballot_w64(odd != 0)) {
+          // some column must not see a value row that holds an infinity or
+          // NaN, and 0 * inf would reach it through the product: key by key,
+          // each column over its own keys only
+          const unsigned char *vr = ringp + (st % S) * STAGE + HALF;
+#pragma unroll 1
+          for (int key = 0; key < SK; ++key) {
+            const int h = key >> 4, gg = (key & 15) >> 2, e = key & 3;
+            float p[CT];
+#pragma unroll
+            for (int i = 0; i < CT; ++i) {
+              const uint32_t w0 = h ? pb[i].z : pb[i].x, w1 = h ? pb[i].w : pb[i].y;
+              const uint32_t pw = __shfl((e >> 1) ? w1 : w0, r + 16 * gg, 64);
+              p[i] = (e & 1) ? __uint_as_float(pw & 0xffff0000u) : __uint_as_float(pw << 16);
+            }
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+              const u32x2 vw = *reinterpret_cast<const u32x2 *>(
+                  vr + key * RB + 16 * ((2 * dt + (g >> 1)) ^ swz(key)) + 8 * (g & 1));
+              const f32x4 vf = {__uint_as_float(vw.x << 16), __uint_as_float(vw.x & 0xffff0000u),
+                                __uint_as_float(vw.y << 16), __uint_as_float(vw.y & 0xffff0000u)};
+#pragma unroll
+              for (int i = 0; i < CT; ++i)
+                if (k0 + key < P[i]) oacc[i][dt] += vf * p[i];
+            }
+          }
+          continue;
+        }
+      }
+      // V^T by the transposing read (see attn_unit), for the two 16-key halves
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        const unsigned char *vp = ringp + (vst ^ (32 * dt));
+        const u32x2 a0 = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                       (__attribute__((address_space(3))) i16x4 *)vp));
+        const u32x2 a1 = __builtin_bit_cast(
+            u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                       (__attribute__((address_space(3))) i16x4 *)(vp + 16 * RB)));
+        const u32x4 av = {a0.x, a0.y, a1.x, a1.y};
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+          oacc[i][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, pb[i]), oacc[i][dt], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));  // the stages fetched past the end
+
+    // the row's own key and value, then the output row
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const float lt = lacc[i].x;  // every row of the product with ones is the column's sum
+      const float M = fmaxf(mx_[i], sown[i]);
+      const float sp = sexp2(mx_[i], M), sc = __builtin_amdgcn_exp2f(sown[i] - M);
+      float inv = 1.f / (lt * sp + sc);
+      if (bad[i]) inv = __int_as_float(0x7fc00000);  // P outside [0, pmax]
+      if (!live[i]) continue;
+      const float *vp = vnew + ((size_t)mrow[i] * Hkv + c) * D + 4 * g;
+      bf16_t *op = out + ((size_t)mrow[i] * Hq + mh[i]) * D + 4 * g;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        const f32x4 o = (oacc[i][dt] * sp + *reinterpret_cast<const f32x4 *>(vp + 16 * dt) * sc) * inv;
+        *reinterpret_cast<u32x2 *>(op + 16 * dt) = u32x2{pack_bf16(o.x, o.y), pack_bf16(o.z, o.w)};
+      }
+    }
+  }
+}
+
 template <typename T, int D>
 static hipError_t attn_t(const void *K, const void *V, Seqs cu, const float *q,
                          const float *knew, const float *vnew, int nctx, float *part, int nch,
@@ -568,6 +954,42 @@ int attention_cpw(int B, int Hkv, int ngroups, int nch) {
   }
   if (cpw > nch) cpw = nch;
   return cpw < 1 ? 1 : (int)cpw;
+}
+
+// query heads of one column group: the tiles carry kTileQ / GH rows
+static int tile_heads(int G) { return G % 8 == 0 ? 8 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
+
+hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int32_t *tiles,
+                          hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_attn_tile_plan, dim3(1), dim3(1024), 0, s, ranges, M, pmax,
+                     kTileQ / tile_heads(Hq / Hkv), tiles);
+  return hipGetLastError();
+}
+
+hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges,
+                           const int32_t *tiles, int M, const float *q, const float *knew,
+                           const float *vnew, void *out, int Hq, int Hkv, int D,
+                           const float *rope, int pmax, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  const int GH = tile_heads(Hq / Hkv);
+  // two workgroups per CU; each takes every gridDim.x-th (tile, column group)
+  const long items = (long)M * (Hq / GH);
+  const dim3 grid((unsigned)(items < resident_waves() / 2 ? items : resident_waves() / 2));
+#define FE_ATTN_TILE(DV, GHV)                                                                     \
+  hipLaunchKernelGGL((k_attn_tile<DV, GHV>), grid, dim3(64 * kTileWaves), 0, s, (const bf16_t *)K,            \
+                     (const bf16_t *)V, ranges, tiles, q, knew, vnew, (bf16_t *)out, Hq, Hkv, rope, pmax)
+#define FE_ATTN_TILE_D(DV)                 \
+  switch (GH) {                            \
+    case 8: FE_ATTN_TILE(DV, 8); break;    \
+    case 4: FE_ATTN_TILE(DV, 4); break;    \
+    case 2: FE_ATTN_TILE(DV, 2); break;    \
+    default: FE_ATTN_TILE(DV, 1); break;   \
+  }
+  if (D == 128) FE_ATTN_TILE_D(128) else FE_ATTN_TILE_D(64)
+#undef FE_ATTN_TILE_D
+#undef FE_ATTN_TILE
+  return hipGetLastError();
 }
 
 hipError_t attention(int dt, const void *K, const void *V, Seqs cu, const float *q,

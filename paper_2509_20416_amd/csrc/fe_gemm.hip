@@ -543,10 +543,6 @@ __global__ __launch_bounds__(256) void k_gemm_mid(const T *__restrict__ A, int l
 // input FC at 34 % and the K/V GEMM of all five layers at 24 % of the bf16
 // peak, against 20-29 % for k_gemm_mid's 128 x 64 tiles.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ constexpr int waitcnt_imm(int vm, int lgkm) {
-  return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8);
-}
-
 constexpr int kBigRows = 128, kBigCols = 128;
 
 // SPLIT: K is split over grid y and each slice's fp32 sums go to splitp
@@ -557,11 +553,11 @@ constexpr int kBigRows = 128, kBigCols = 128;
 // 128 x 128 tiles are 4, 2, 2, 4; the 256 x 128 tiles of up to 256 rows (one
 // row block, so the weights are streamed once) are 4, 4, 4, 2.
 template <int RT, int NTW, int WM, int WN, int S, class Epi, bool SPLIT = false>
-__global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A, int lda, ARows arows,
+__global__ __launch_bounds__(64 * WM * WN) void k_gemm_tile(const bf16_t *__restrict__ A, int lda, ARows arows,
                                                    int M, int K, Epi epi, float *__restrict__ splitp,
                                                    int ldp) {
   constexpr int NW = WM * WN;
-  static_assert(NW == 8, "eight waves");
+  static_assert(NW == 8 || NW == 4, "two waves or one per SIMD");
   constexpr int BM = 16 * RT * WM, BN = 16 * NTW * WN, KC = 64;
   constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
   constexpr int AI = BM / 8 / NW, WI = BN / 8 / NW, CNT = AI + WI;  // 1 KB loads per wave per chunk
@@ -571,7 +567,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A,
   // columns per instruction) land on distinct banks; one float longer for
   // the LM head's scan (a thread per row: consecutive rows on distinct banks)
   constexpr int LDT = BN + (std::is_same<Epi, EpiLm<bf16_t>>::value ? 1 : 4), TILE = BM * LDT * 4;
-  constexpr int SMEM = S * STAGE > TILE ? S * STAGE : TILE;
+  constexpr int SMEM = SPLIT || S * STAGE > TILE ? S * STAGE : TILE;
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
   int m0 = 0, Mb = M;  // first row of this block, rows in it
   if constexpr (SPLIT) {

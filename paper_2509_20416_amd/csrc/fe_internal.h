@@ -55,6 +55,11 @@ __device__ __forceinline__ void lds_dma16(const void *src, void *lds) {
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// s_waitcnt immediate the compiler sees: at most vm vector-memory and lgkm LDS
+// operations still in flight (lgkm 15: not waited for)
+__device__ __forceinline__ constexpr int waitcnt_imm(int vm, int lgkm) {
+  return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8);
+}
 
 // ---- cross-lane reductions in registers (no LDS traffic) -------------------------
 // DPP controls: quad_perm [1,0,3,2] (lane^1), [2,3,0,1] (lane^2), row_half_mirror
@@ -434,6 +439,18 @@ hipError_t attention(int dt, const void *K, const void *V, Seqs seqs,
                      const float *q, const float *knew, const float *vnew, int nctx,
                      float *part, int nch, int nch_ld, int cpw, void *out, int B, int Hq,
                      int Hkv, int D, const float *rope, int cascade, int pmax, hipStream_t s);
+// Attention of the M rows of a bf16 prefill, in tiles of consecutive rows that
+// share their sequence's keys: row m (q [M, Hq, D], own key and value knew /
+// vnew [M, Hkv, D], all unrotated fp32) sees cache rows ranges[2m] ..
+// ranges[2m + 1] - 1 and its own key, at position P = the range's length; a row
+// whose P lies outside [0, pmax] gets a NaN row.  tiles: the plan of the same
+// ranges from attn_tile_plan (at most M tiles: M + 2 ints).
+hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int32_t *tiles,
+                          hipStream_t s);
+hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges,
+                           const int32_t *tiles, int M, const float *q, const float *knew,
+                           const float *vnew, void *out, int Hq, int Hkv, int D,
+                           const float *rope, int pmax, hipStream_t s);
 // kAttnChunk-key chunks per attention work unit for a launch of B sequences
 // over nch = ceil(max_prefix / kAttnChunk) chunks
 int attention_cpw(int B, int Hkv, int ngroups, int nch);

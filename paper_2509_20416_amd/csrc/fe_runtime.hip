@@ -151,6 +151,10 @@ Layout layout_of(const fe_config &c) {
 // are faster (measured on the 8B shapes: 192 rows 205 against 278 us, 256
 // rows 219 against 287 us).
 constexpr int kTiledRows = kGemmMaxRows + 1, kFusedRows = 16;
+// rows of a bf16 prefill step from which the attention runs over tiles of rows
+// (k_attn_tile): one workgroup streams a tile's keys, so fewer rows leave the
+// chip idle where the row-by-row units split each row's keys
+constexpr int kAttnTileRows = 64;
 
 struct UpdLayout {
   size_t cat, X, an, ssq, splitk, total;
@@ -160,6 +164,7 @@ struct UpdLayout {
   // one 256-row slice)
   size_t q, knew, vnew, ao, Xp, sb, ranges, part;
   int nch_ld;
+  size_t part_floats;
 };
 
 UpdLayout upd_layout_of(const fe_config &c, size_t C) {
@@ -188,7 +193,8 @@ UpdLayout upd_layout_of(const fe_config &c, size_t C) {
     U.Xp = take(C * d * 4);
     U.sb = take(C * (size_t)c.intermediate * es);
     U.ranges = take(C * 2 * 4);
-    U.part = take(rows * c.n_q_heads * ((size_t)U.nch_ld * (D + 2) + 1) * 4);
+    U.part_floats = rows * c.n_q_heads * ((size_t)U.nch_ld * (D + 2) + 1);
+    U.part = take(U.part_floats * 4);
   }
   U.total = o;
   return U;
@@ -1147,10 +1153,33 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
   // bf16 chunks of more rows than one batched launch takes: every GEMM as one
   // 2-D tiled launch over all rows (each weight matrix streamed once per chunk)
   const bool tiled = dt && Mc >= kTiledRows;
+  // the tiles' plan takes the place of the attention partials, which the tiled
+  // attention does not need; a split set by the caller keeps the split kernels
+  const bool attn_tiles = dt && Mc >= kAttnTileRows && h->attn_split == 0 &&
+                          U.part_floats >= (size_t)Mc + 2;
+  int32_t *tiles = (int32_t *)part;
+  if (attn_tiles && c.n_layers > 1) FE_TRY(attn_tile_plan(ranges, Mc, pmax, Hq, Hkv, tiles, s));
   for (int l = 0; l < c.n_layers; ++l) {
     const Range range("fe.prefill_layer");
     const fe_layer_weights &lw = h->layers[l];
     FE_TRY(rmsnorm_rows(dt, X, Mc, 1, 0, d, 0, lw.attn_norm, an, d, c.rms_eps, s));
+    if (l + 1 == c.n_layers) {
+      // the last layer only keys its input: nothing reads its output state, so
+      // its queries, attention and MLP are not run
+      const KvCacheArgs ka{lw.wk, lw.wv, d, D, Hkv, positions, dst_rows, (long)cache->rows,
+                           c.max_prefix, rope, cache->k[l], cache->v[l]};
+      if (tiled) {
+        FE_TRY(gemm_kv_rows(an, d, 0, Mc, 1, &ka, nullptr, s));
+        break;
+      }
+      for (int s0 = 0; s0 < Mc; s0 += kGemmMaxRows) {
+        KvCacheArgs kr = ka;
+        kr.positions += s0;
+        kr.dst_rows += s0;
+        FE_TRY(gemm_kvcache(dt, an + (size_t)s0 * d * es, d, std::min(kGemmMaxRows, Mc - s0), kr, s, ss));
+      }
+      break;
+    }
     if (tiled) {
       // q, K, V of every row (fp32, unrotated: the attention rotates them)
       FE_TRY(gemm_resid_rows(an, d, Mc, d, lw.wq, qd, q, qd, s));
@@ -1167,7 +1196,10 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
     // every row's K/V is in the cache before any row's attention reads it
     FE_TRY(kv_scatter(dt, knew, vnew, Mc, Hkv, D, positions, dst_rows, (long)cache->rows,
                       c.max_prefix, rope, dt ? 0 : 1, cache->k[l], cache->v[l], s));
-    for (int s0 = 0; s0 < Mc; s0 += kGemmMaxRows) {
+    if (attn_tiles)
+      FE_TRY(attention_tiles(cache->k[l], cache->v[l], ranges, tiles, Mc, q, knew, vnew, ao, Hq, Hkv,
+                             D, rope, pmax, s));
+    for (int s0 = 0; s0 < Mc && !attn_tiles; s0 += kGemmMaxRows) {
       const int Ms = std::min(kGemmMaxRows, Mc - s0);
       const int cpw = h->attn_split > 0 ? h->attn_split : attention_cpw(Ms, Hkv, 1, nch);
       FE_TRY(attention(dt, cache->k[l], cache->v[l], Seqs{ranges + 2 * s0, 1},

@@ -1,0 +1,80 @@
+"""The prefill's attention over tiles of rows (bf16, 64 rows and more) against
+the split kernels that fewer rows take (selected by an explicit attention
+split): the same arithmetic up to the order of the sums and the split of the
+keys, so cache rows agree within the storage tolerance, and NaN rows are the
+same ones."""
+import numpy as np
+import pytest
+
+from fe_synth import configs as C
+from fe_synth import make_update_rows, make_weights
+from fe_synth.gen import float_tensor
+from tests.parity import TOL, assert_rows_close
+
+pytestmark = pytest.mark.gpu
+SELF = lambda c: c.with_(cascade_ctx="self", name=c.name + "_self")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _update(cfg, w, up, split, max_prefix):
+    """Caches (fp64 values) after one update; split 0 takes the tiles."""
+    import torch
+    from paper_2509_20416_amd import Drafter
+    from paper_2509_20416_amd.drafter import to_device
+    dr = Drafter(cfg, w, max_batch=1, max_prefix=max_prefix, max_topk=cfg.topk)
+    dr.set_attention_split(split)
+    shape = (up.cache_rows, cfg.n_kv_heads, cfg.head_dim)
+    kv = [[to_device(float_tensor(f"tiles.{n}{l}", shape, 5, cfg.dtype), cfg.dtype, dr.device)
+           for l in range(cfg.n_layers)] for n in "kv"]
+    dr.kv_update(to_device(up.features, cfg.dtype, dr.device), to_device(up.tokens, "i32", dr.device),
+                 to_device(up.positions, "i32", dr.device), to_device(up.dst_rows, "i32", dr.device),
+                 *kv)
+    torch.cuda.synchronize()
+    got = [t.double().cpu().numpy().reshape(up.cache_rows, -1) for side in kv for t in side]
+    dr.close()
+    return got
+
+
+CASES = [  # rows per sequence, prefix per sequence
+    (SELF(C.SMALL_GQA_BF16), [64], [0]),                        # the fewest rows; 32-row tiles
+    (SELF(C.SMALL_GQA_BF16), [33, 1, 31, 65, 2], [0, 700, 31, 32, 1]),  # runs across tile edges
+    (SELF(C.SMALL_GQA8_BF16_D128), [17, 100], [0, 333]),        # 16-row tiles, head dim 128
+    (SELF(C.SMALL_MHA_BF16_D128), [129, 140], [5, 0]),          # 128-row tiles
+    (SELF(C.SMALL_GQA2_BF16), [70, 63], [0, 64]),               # 64-row tiles
+    (SELF(C.SMALL_GQA_BF16), [1] * 70, list(range(70))),        # every row a run of its own
+    (SELF(C.SMALL_GQA_BF16), [1100], [0]),                      # two chunks, more runs than one scan
+]
+
+
+@pytest.mark.parametrize("cfg,acc,plens", CASES, ids=[f"{c.name}-{len(a)}x{a[0]}" for c, a, _ in CASES])
+def test_tiles_match_split_kernels(cfg, acc, plens):
+    acc, plens = np.asarray(acc, np.int32), np.asarray(plens, np.int32)
+    cap = int((acc + plens).max())
+    up = make_update_rows(cfg, acc, plens, capacity=cap, seed=11)
+    w = make_weights(cfg, 3)
+    for i, (a, b) in enumerate(zip(_update(cfg, w, up, 0, cap), _update(cfg, w, up, 4, cap))):
+        assert_rows_close(f"array {i}", a[up.dst_rows], b[up.dst_rows], TOL["bf16"])
+
+
+def test_tiles_keep_nan_rows_apart():
+    """A row whose token is outside the vocabulary is NaN, and with it the later
+    rows of its sequence (they see its key), but no earlier row of its tile; a
+    row whose position-0 row lies before the cache is NaN by itself."""
+    cfg = SELF(C.SMALL_GQA_BF16)
+    up = make_update_rows(cfg, np.array([80, 40]), np.array([0, 9]), capacity=96, seed=12)
+    up.tokens[50] = cfg.target_vocab + 5
+    up.positions[3] = 60          # dst 3 - 60 < 0
+    w = make_weights(cfg, 3)
+    tiles, split = (_update(cfg, w, up, s, 96) for s in (0, 4))
+    for i, (a, b) in enumerate(zip(tiles, split)):
+        np.testing.assert_array_equal(np.isnan(a), np.isnan(b), err_msg=f"array {i}")
+        ok = up.dst_rows[~np.isnan(b[up.dst_rows]).any(1)]
+        assert_rows_close(f"array {i}", a[ok], b[ok], TOL["bf16"])
+    last = np.isnan(tiles[cfg.n_layers - 1][up.dst_rows]).any(1)  # the deepest layer's keys
+    assert last[50:80].all() and last[3] and not last[:3].any() and not last[80:].any()
