@@ -25,6 +25,7 @@
 //    tile; gate/up tiles pair gate row c with up row c.
 #include "fe_internal.h"
 #include <type_traits>
+#include <utility>
 
 namespace fe {
 
@@ -139,6 +140,13 @@ __device__ __forceinline__ void accum_staged(const T *__restrict__ A, int lda, c
 template <class E, class = void> struct SlicedEpi { static constexpr bool value = false; };
 template <class E> struct SlicedEpi<E, decltype((void)E::kSliced)> {
   static constexpr bool value = E::kSliced;
+};
+
+// Epilogues with a member bx: the workgroup's column block, where it is not
+// blockIdx.x (k_gemm_tile).
+template <class E, class = void> struct HasBlock { static constexpr bool value = false; };
+template <class E> struct HasBlock<E, decltype((void)std::declval<E>().bx)> {
+  static constexpr bool value = true;
 };
 
 // ---------------------------------------------------------------------------
@@ -526,141 +534,173 @@ __global__ __launch_bounds__(256) void k_gemm_mid(const T *__restrict__ A, int l
 }
 
 // ---------------------------------------------------------------------------
-// Many rows, matrix-core bound (the cache update's and the prefill's row
-// blocks: bf16, K a multiple of 64): 128 x 128 output tiles, eight waves as 2
-// row groups x 4 column groups of 64 x 32, so two waves share each SIMD.  The
-// ring and its swizzle are k_gemm_mid's; the schedule is software-pipelined
-// over the two 32-wide K steps of a chunk:
+// Many rows, matrix-core bound (the cache update, the prefill, the batched
+// Q/K/V and LM head: bf16, K a multiple of 64).  Eight waves, two per SIMD, WM
+// row groups x WN column groups of RT x NTW 16 x 16 tiles; column tile f of
+// wave column wn is tile f * WN + wn of the workgroup.  The ring and its
+// swizzle are k_gemm_mid's; the schedule is software-pipelined over the two
+// 32-wide K steps of a chunk:
 //   read step-1 fragments of chunk c | products of step 0 (read last round)
 //   wait: chunk c+1 landed, every read of chunk c done; barrier
-//   refill chunk c's slot with chunk c+S | read step-0 fragments of chunk c+1
+//   refill chunk c's slot with chunk c+S, read step-0 fragments of chunk c+1 |
 //   products of step 1
-// so every product's operands were read while other products ran.  Waits are
-// compiler-visible s_waitcnt immediates and the phases are fenced with
-// scheduling barriers: with inline-asm waits the compiler hoisted the barrier
-// (and its lgkmcnt(0)) above the products, serialising LDS latency.  At 1024
-// rows (8B shapes, epilogues included) the fusion GEMM runs at 33 %, the
-// input FC at 34 % and the K/V GEMM of all five layers at 24 % of the bf16
-// peak, against 20-29 % for k_gemm_mid's 128 x 64 tiles.
+// with the loads and reads of a phase woven between the products, one row of
+// tiles at a time.  A wave issues in order: with all loads and reads ahead of
+// the products, every wave queued behind the others' at the same moment and
+// the matrix cores waited (256 x 256 tiles, K 12288: 274 us a tile, woven 236;
+// 128 x 128: 124 and 119).  Waits are compiler-visible s_waitcnt immediates and
+// the phases are fenced with scheduling barriers: with inline-asm waits the
+// compiler hoisted the barrier (and its lgkmcnt(0)) above the products.
+// What bounds it is the loop inside a CU, not memory: 64 workgroups take as
+// long as 256, and a deeper ring changes nothing.  Larger tiles read fewer
+// fragments per product, so they run at a higher rate while they fill the
+// chip (1024 rows x 28672 columns, K 4096: 315 us with 128 x 128, 213 with
+// 256 x 256, 200 with 256 x 224 tiles, whose last round is full).
 // ---------------------------------------------------------------------------
-constexpr int kBigRows = 128, kBigCols = 128;
-
+//
 // SPLIT: K is split over grid y and each slice's fp32 sums go to splitp
 // (slice y at y * M * ldp, row m at m * ldp) for a second launch that sums them
 // and runs the epilogue; the row blocks of grid z then cover rows
 // arows.row(m) of A directly (no epilogue slicing).
-// RT x NTW 16 x 16 tiles per wave, WM x WN waves (eight): the cache update's
-// 128 x 128 tiles are 4, 2, 2, 4; the 256 x 128 tiles of up to 256 rows (one
-// row block, so the weights are streamed once) are 4, 4, 4, 2.
 template <int RT, int NTW, int WM, int WN, int S, class Epi, bool SPLIT = false>
-__global__ __launch_bounds__(64 * WM * WN) void k_gemm_tile(const bf16_t *__restrict__ A, int lda, ARows arows,
+__global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A, int lda, ARows arows,
                                                    int M, int K, Epi epi, float *__restrict__ splitp,
-                                                   int ldp) {
+                                                   int ldp, int nb) {
   constexpr int NW = WM * WN;
-  static_assert(NW == 8 || NW == 4, "two waves or one per SIMD");
+  static_assert(NW == 8, "eight waves");
   constexpr int BM = 16 * RT * WM, BN = 16 * NTW * WN, KC = 64;
   constexpr int ABYTES = BM * 128, STAGE = ABYTES + BN * 128;
-  constexpr int AI = BM / 8 / NW, WI = BN / 8 / NW, CNT = AI + WI;  // 1 KB loads per wave per chunk
+  // 1 KB loads of a chunk: AN + WI, dealt to the waves in turn; CNT per wave
+  constexpr int AN = BM / 8, LN = AN + BN / 8, CNT = (LN + NW - 1) / NW;
   static_assert(S >= 2 && (S - 1) * CNT <= 63, "vmcnt range");
-  // epilogue tile rows 4 floats longer than the span: 16-byte aligned for
-  // the epilogues' vector reads, and the accumulator writes (4 rows x 16
-  // columns per instruction) land on distinct banks; one float longer for
-  // the LM head's scan (a thread per row: consecutive rows on distinct banks)
-  constexpr int LDT = BN + (std::is_same<Epi, EpiLm<bf16_t>>::value ? 1 : 4), TILE = BM * LDT * 4;
+  // The epilogue takes FP of the NTW column tiles per pass.  Its tile rows are
+  // 4 floats longer than the span: 16-byte aligned for the vector reads, and
+  // the accumulator writes (4 rows x 16 columns per instruction) land on
+  // distinct banks; one float longer for the LM head's scan (a thread per row:
+  // consecutive rows on distinct banks)
+  constexpr bool kLm = std::is_same<Epi, EpiLm<bf16_t>>::value;
+  constexpr int kMaxTile = 140 * 1024;
+  constexpr int FP = BM * (BN + 4) * 4 <= kMaxTile ? NTW : (NTW + 1) / 2;
+  constexpr int PN = 16 * FP * WN, LDT = PN + (kLm ? 1 : 4), TILE = BM * LDT * 4;
+  static_assert(TILE <= kMaxTile && PN % 32 == 0 && (!kLm || FP == NTW), "epilogue passes");
   constexpr int SMEM = SPLIT || S * STAGE > TILE ? S * STAGE : TILE;
+  static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
+  // Which tile: workgroups are dealt to the 8 XCDs in turn, so XCD i's share
+  // of the launch order is every 8th; it takes a contiguous run of the tiles in
+  // the order row block (nb per group), columns, K slice, group, whose tiles
+  // share their weights and A rows in the XCD's L2 (K/V of five layers, 1024
+  // rows: 114 us in launch order, 107 so).
+  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  if (gridDim.y * gridDim.z > 1) {
+    const int total = gridDim.x * gridDim.y * gridDim.z;
+    const int pid = bx + gridDim.x * (by + gridDim.y * bz), xcd = pid & 7;
+    int id = xcd * (total >> 3) + min(xcd, total & 7) + (pid >> 3);
+    bz = id % nb;
+    id /= nb;
+    bx = id % gridDim.x;
+    id /= gridDim.x;
+    by = id % gridDim.y;
+    bz += (id / gridDim.y) * nb;
+  }
+  if constexpr (HasBlock<Epi>::value) epi.bx = bx;
   int m0 = 0, Mb = M;  // first row of this block, rows in it
   if constexpr (SPLIT) {
-    m0 = blockIdx.z * BM;
+    m0 = bz * BM;
     Mb = min(BM, M - m0);
   } else if constexpr (SlicedEpi<Epi>::value) {
     const bf16_t *a = A;
-    epi.slice(blockIdx.z, BM, a, M);
+    epi.slice(bz, BM, a, M);
     A = a;
     Mb = M;
   }  // else one row block of at most BM rows
   if (Mb <= 0) return;  // the whole workgroup: past the last row block
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wm = wave / WN, wn = wave % WN;
-  const int c0 = blockIdx.x * BN;
+  const int c0 = bx * BN;
   // this workgroup's chunks of K: [cb, cb + nch)
   const int nchk = K / KC;
-  const int cb = SPLIT ? (int)((long)nchk * blockIdx.y / gridDim.y) : 0;
-  const int nch = SPLIT ? (int)((long)nchk * (blockIdx.y + 1) / gridDim.y) - cb : nchk;
-  // the lane's slot in each of its load instructions and the source there
-  // (rows past M repeat row M-1, columns past the end the last column: their
-  // products land in outputs that are never stored)
-  const bf16_t *asrc[AI], *wsrc[WI];
+  const int cb = SPLIT ? (int)((long)nchk * by / gridDim.y) : 0;
+  const int nch = SPLIT ? (int)((long)nchk * (by + 1) / gridDim.y) - cb : nchk;
+  // the lane's source in each of its loads: load j of a wave fills the 1 KB
+  // (eight rows) j * NW + wave of the stage, A rows first (rows past M repeat
+  // row M-1, columns past the end the last column: their products land in
+  // outputs that are never stored).  Where the loads don't divide evenly, the
+  // last ones repeat the stage's last kilobyte, so every wave issues CNT.
+  const bf16_t *src[CNT];
+  int dst[CNT];
 #pragma unroll
-  for (int j = 0; j < AI; ++j) {
-    const int q = (j * NW + wave) * 64 + lane, row = q >> 3;
-    asrc[j] = A + (size_t)arows.row(m0 + min(row, Mb - 1)) * lda + ((q & 7) ^ ((row >> 1) & 7)) * 8;
+  for (int j = 0; j < CNT; ++j) {
+    const int q = min(j * NW + wave, LN - 1), row = (q < AN ? q : q - AN) * 8 + (lane >> 3);
+    const int piece = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    src[j] = q < AN ? A + (size_t)arows.row(m0 + min(row, Mb - 1)) * lda + piece
+                    : epi.wrow(min(c0 + row, epi.nvcols - 1)) + piece;
+    dst[j] = q * 1024;
   }
-#pragma unroll
-  for (int j = 0; j < WI; ++j) {
-    const int q = (j * NW + wave) * 64 + lane, n = q >> 3;
-    wsrc[j] = epi.wrow(min(c0 + n, epi.nvcols - 1)) + ((q & 7) ^ ((n >> 1) & 7)) * 8;
-  }
-  // chunk ch into its ring slot (past the end the last chunk is fetched again,
-  // so every wave issues the same count)
-  auto issue = [&](int ch) {
-    char *st = smem + (ch % S) * STAGE;
-    const int k = (cb + min(ch, nch - 1)) * KC;
-#pragma unroll
-    for (int j = 0; j < AI; ++j) lds_dma16(asrc[j] + k, st + (j * NW + wave) * 1024);
-#pragma unroll
-    for (int j = 0; j < WI; ++j) lds_dma16(wsrc[j] + k, st + ABYTES + (j * NW + wave) * 1024);
-  };
+  auto issue1 = [&](int j, char *st, int k) { lds_dma16(src[j] + k, st + dst[j]); };
+  // K offset of chunk ch (past the end the last chunk is fetched again)
+  auto koff = [&](int ch) { return (cb + min(ch, nch - 1)) * KC; };
   f32x4 acc[RT][NTW];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int f = 0; f < NTW; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int mrow0 = wm * 16 * RT, ncol0 = wn * NTW * 16;
+  const int mrow0 = wm * 16 * RT;
+  auto afrag = [&](const char *st, int ks, int i) {
+    return *reinterpret_cast<const u32x4 *>(st + ring_slot(mrow0 + i * 16 + r, ks * 4 + g) * 16);
+  };
+  auto bfrag = [&](const char *st, int ks, int f) {
+    return *reinterpret_cast<const u32x4 *>(
+        st + ABYTES + ring_slot((f * WN + wn) * 16 + r, ks * 4 + g) * 16);
+  };
   u32x4 a0[RT], b0[NTW], a1[RT], b1[NTW];
-  auto frags = [&](const char *st, int ks, u32x4 (&af)[RT], u32x4 (&bf)[NTW]) {
+  // the products of fragments (ca, cb_), and between them the reads of step ks
+  // of the chunk at `rd` into (na, nb) and, with LOAD, the loads into `ld`
+  auto phase = [&](auto load, const u32x4 (&ca)[RT], const u32x4 (&cb_)[NTW], const char *rd, int ks,
+                   u32x4 (&na)[RT], u32x4 (&nb)[NTW], char *ld, int k) {
 #pragma unroll
-    for (int f = 0; f < NTW; ++f)
-      bf[f] = *reinterpret_cast<const u32x4 *>(st + ABYTES + ring_slot(ncol0 + f * 16 + r, ks * 4 + g) * 16);
+    for (int i = 0; i < RT; ++i) {
+      if constexpr (decltype(load)::value)
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
-      af[i] = *reinterpret_cast<const u32x4 *>(st + ring_slot(mrow0 + i * 16 + r, ks * 4 + g) * 16);
+        for (int j = i * CNT / RT; j < (i + 1) * CNT / RT; ++j) issue1(j, ld, k);
+#pragma unroll
+      for (int f = i * NTW / RT; f < (i + 1) * NTW / RT; ++f) nb[f] = bfrag(rd, ks, f);
+      na[i] = afrag(rd, ks, i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < NTW; ++f) mma16<bf16_t>(acc[i][f], ca[i], cb_[f]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  auto products = [&](const u32x4 (&af)[RT], const u32x4 (&bf)[NTW]) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+  for (int st = 0; st < S; ++st)
 #pragma unroll
-      for (int f = 0; f < NTW; ++f) mma16<bf16_t>(acc[i][f], af[i], bf[f]);
-  };
-#pragma unroll
-  for (int st = 0; st < S; ++st) issue(st);
+    for (int j = 0; j < CNT; ++j) issue1(j, smem + st * STAGE, koff(st));
   __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * CNT, 15));  // chunk 0 (this wave's part)
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  frags(smem, 0, a0, b0);
+#pragma unroll
+  for (int f = 0; f < NTW; ++f) b0[f] = bfrag(smem, 0, f);
+#pragma unroll
+  for (int i = 0; i < RT; ++i) a0[i] = afrag(smem, 0, i);
   for (int ch = 0; ch < nch; ++ch) {
     // the step-0 fragments (read during the last products) are in
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
     __builtin_amdgcn_sched_barrier(0);
-    frags(smem + (ch % S) * STAGE, 1, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    products(a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
+    char *slot = smem + (ch % S) * STAGE;
+    phase(std::false_type{}, a0, b0, slot, 1, a1, b1, nullptr, 0);
     // chunk ch+1 landed (this wave's part) and every read of chunk ch is done;
     // the barrier extends both to the workgroup
     __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 2) * CNT, 0));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    issue(ch + S);  // into chunk ch's slot
-    if (ch + 1 < nch) frags(smem + ((ch + 1) % S) * STAGE, 0, a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    products(a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
+    // after the last chunk the reads take what its refetch left: unused
+    phase(std::true_type{}, a1, b1, smem + ((ch + 1) % S) * STAGE, 0, a0, b0, slot, koff(ch + S));
   }
   // the chunks fetched past the end land before the ring becomes the tile
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
   if constexpr (SPLIT) {
-    float *dst = splitp + ((size_t)blockIdx.y * M + m0) * ldp + c0;
+    float *out = splitp + ((size_t)by * M + m0) * ldp + c0;
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
@@ -668,38 +708,84 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_tile(const bf16_t *__rest
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int m = mrow0 + i * 16 + 4 * g + v;
-          if (m < Mb) dst[(size_t)m * ldp + ncol0 + f * 16 + r] = acc[i][f][v];
+          if (m < Mb) out[(size_t)m * ldp + (f * WN + wn) * 16 + r] = acc[i][f][v];
         }
     return;
   }
-  __syncthreads();
   float(*tile)[LDT] = reinterpret_cast<float(*)[LDT]>(smem);
 #pragma unroll
-  for (int i = 0; i < RT; ++i)
+  for (int f0 = 0; f0 < NTW; f0 += FP) {
+    __syncthreads();
 #pragma unroll
-    for (int f = 0; f < NTW; ++f)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) tile[mrow0 + i * 16 + 4 * g + v][ncol0 + f * 16 + r] = acc[i][f][v];
-  __syncthreads();
-  epi.finish(&tile[0][0], LDT, Mb, c0, BN, typename Epi::Pre{});
+      for (int f = f0; f < f0 + FP && f < NTW; ++f)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          tile[mrow0 + i * 16 + 4 * g + v][((f - f0) * WN + wn) * 16 + r] = acc[i][f][v];
+    __syncthreads();
+    epi.finish(&tile[0][0], LDT, Mb, c0 + f0 * WN * 16, 16 * WN * min(FP, NTW - f0), typename Epi::Pre{});
+  }
 }
 
-// Launch of k_gemm_tile over ncols virtual columns and nz row blocks (of
-// kBigRows): a three-stage ring when the grid is about one workgroup per CU
-// (96 KB of LDS: one workgroup per CU), else two stages, which lets two
-// workgroups share a CU (measured at 1024 rows: fusion and input FC 120 and
-// 78 us with three stages against 134 and 86 with two; the K/V GEMM of five
-// layers 103 us with two stages against 120 with three).
-template <class Epi>
-static hipError_t launch_tile(const bf16_t *A, int lda, int M, int K, const Epi &e, int ncols, int nz,
-                              hipStream_t s) {
-  const dim3 grid((ncols + kBigCols - 1) / kBigCols, 1, nz);
-  if ((long)grid.x * nz <= 288)
-    hipLaunchKernelGGL((k_gemm_tile<4, 2, 2, 4, 3, Epi>), grid, dim3(512), 0, s, A, lda, kDenseRows, M,
-                       K, e, nullptr, 0);
-  else
-    hipLaunchKernelGGL((k_gemm_tile<4, 2, 2, 4, 2, Epi>), grid, dim3(512), 0, s, A, lda, kDenseRows, M,
-                       K, e, nullptr, 0);
+// Tile shapes of the many-row GEMMs and what a 64-wide K chunk of one tile
+// takes (ns, one workgroup per CU, measured at K 12288).  A launch takes the
+// shape whose rounds of workgroups cost least; K may be split over up to
+// max_slices workgroups per tile where the caller sums the slices, which costs
+// a write and a read of every slice.
+enum TileShape { kTile128x128 = 0, kTile128x192, kTile128x256, kTile256x224, kTile256x256, kTileShapes };
+struct TilePick {
+  int shape, ks;
+};
+constexpr int kTileM[kTileShapes] = {128, 128, 128, 256, 256};
+constexpr int kTileN[kTileShapes] = {128, 192, 256, 224, 256};
+constexpr int kTileNs[kTileShapes] = {620, 750, 830, 1180, 1240};
+static TilePick pick_tile(int M, int ncols, int K, int groups, int max_slices) {
+  const long nch = K / 64;
+  TilePick best{kTile128x128, 1};
+  double cost = 1e30;
+  for (int t = 0; t < kTileShapes; ++t)
+    for (int ks = 1; ks <= max_slices; ++ks) {
+      if (ks > 1 && nch / ks < 8) break;  // at least 8 chunks of K per slice
+      const long wgs = (long)((M + kTileM[t] - 1) / kTileM[t]) * groups * ((ncols + kTileN[t] - 1) / kTileN[t]) * ks;
+      const double rounds = (double)((wgs + 255) / 256);
+      // ns; a round also fills and drains its ring and writes its tile (about
+      // 6 us); slices move at about 4 bytes per ps
+      double c = rounds * ((double)((nch + ks - 1) / ks) * kTileNs[t] + 6000.0);
+      if (ks > 1) c += (double)ks * M * ncols * 8 / 4000.0;
+      if (c < cost) {
+        cost = c;
+        best = {t, ks};
+      }
+    }
+  return best;
+}
+
+// Launch of k_gemm_tile over ncols virtual columns of M rows (and `groups`
+// groups of them, TileKv's layers), grid z over the row blocks.  128 x 128
+// tiles take a three-stage ring when the grid is about one workgroup per CU
+// (96 KB of LDS), else two stages, which lets two workgroups share a CU (1024
+// rows x 6144 columns, K 4096: 75 us with three stages, 59 with two).
+template <class Epi, bool SPLIT>
+static hipError_t launch_tile(const TilePick &p, const bf16_t *A, int lda, int M, int K, const Epi &e,
+                              int groups, float *sp, int ldp, hipStream_t s) {
+  const int nb = (M + kTileM[p.shape] - 1) / kTileM[p.shape];  // row blocks per group
+  const dim3 grid((e.nvcols + kTileN[p.shape] - 1) / kTileN[p.shape], p.ks,
+                  nb * groups);
+#define FE_TILE(RT, NTW, WM, WN, S)                                                             \
+  hipLaunchKernelGGL((k_gemm_tile<RT, NTW, WM, WN, S, Epi, SPLIT>), grid, dim3(512), 0, s, A,   \
+                     lda, kDenseRows, M, K, e, sp, ldp, nb)
+  switch (p.shape) {
+    case kTile128x128:
+      if ((long)grid.x * grid.y * grid.z <= 288) FE_TILE(4, 2, 2, 4, 3);
+      else FE_TILE(4, 2, 2, 4, 2);
+      break;
+    case kTile128x192: FE_TILE(4, 3, 2, 4, 3); break;
+    case kTile128x256: FE_TILE(4, 4, 2, 4, 3); break;
+    case kTile256x224: FE_TILE(4, 7, 4, 2, 2); break;
+    default: FE_TILE(8, 4, 2, 4, 2); break;
+  }
+#undef FE_TILE
   return hipGetLastError();
 }
 
@@ -839,6 +925,39 @@ __global__ __launch_bounds__(kRowThreads) void k_resid_rows(const float *__restr
   }
 }
 
+// Row finish of a many-row storing GEMM (the fusion FC): sums the ks fp32
+// slices of a row in slice order, stores the row in bf16 and copies the
+// embedding row of its token next to it (NaN for a token outside [0, vocab)).
+// One workgroup per row, eight adjacent columns per thread.
+__global__ __launch_bounds__(256) void k_store_rows(const float *__restrict__ splitp, int ldp, int ks,
+                                                    int M, int ncols, bf16_t *__restrict__ out,
+                                                    int ldo, const bf16_t *__restrict__ embed,
+                                                    const int32_t *__restrict__ tokens, int vocab,
+                                                    bf16_t *__restrict__ gather_out, int ld_gather,
+                                                    int d) {
+  const int m = blockIdx.x;
+  const size_t slice = (size_t)M * ldp;
+  const int tok = embed ? tokens[m] : -1;
+  for (int e = 8 * threadIdx.x; e < ncols; e += 8 * 256) {
+    const float *src = splitp + (size_t)m * ldp + e;
+    float v[8];
+    tile8(src, 4, v);
+    for (int y = 1; y < ks; ++y) {
+      float w[8];
+      tile8(src + y * slice, 4, w);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] += w[j];
+    }
+    store8<bf16_t>(out + (size_t)m * ldo + e, v);
+  }
+  if (!embed) return;
+  const bool bad = tok < 0 || tok >= vocab;
+  const u32x4 nan8 = {0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u};
+  const u32x4 *src = reinterpret_cast<const u32x4 *>(embed + (size_t)(bad ? 0 : tok) * d);
+  u32x4 *dst = reinterpret_cast<u32x4 *>(gather_out + (size_t)m * ld_gather);
+  for (int e = threadIdx.x; e < d / 8; e += 256) dst[e] = bad ? nan8 : src[e];
+}
+
 // ---------------------------------------------------------------------------
 // Epilogues.
 // ---------------------------------------------------------------------------
@@ -864,6 +983,7 @@ template <typename T> struct EpiStore {
   int vocab;
   T *gather_out;
   int ld_gather, d, B;
+  int bx = -1;
   __device__ const T *wrow(int c) const { return w + (size_t)c * ldw; }
   // a thread per element when that is one round, else per (row, 8 adjacent
   // columns) with one vector store where aligned
@@ -887,7 +1007,7 @@ template <typename T> struct EpiStore {
     }
     if (embed) {  // the embedding row e_{t+1} of every sequence, copied next to g_t
       constexpr int E = Elt<T>::kPer16B;
-      for (int b = blockIdx.x; b < B; b += gridDim.x) {
+      for (int b = bx < 0 ? (int)blockIdx.x : bx; b < B; b += gridDim.x) {
         const int tok = tokens[b];
         T *dst = gather_out + (size_t)b * ld_gather;
         if (tok < 0 || tok >= vocab) {
@@ -1120,56 +1240,85 @@ template <typename T> struct EpiKvCache {
   __device__ void finish(float *tile, int ldt, int M, int c0, int span, const Pre &) const {
     const int kvd = a.Hkv * a.D, D = a.D;
     const float qnan = __int_as_float(0x7fc00000);
-    const bool one = M * span <= (int)blockDim.x;
-    const int per = one ? 1 : 8, gpr = span / per;
-    for (int idx = threadIdx.x; idx < M * gpr; idx += blockDim.x) {
-      const int m = idx / gpr, c = (idx % gpr) * per, vc = c0 + c;
-      if (vc >= nvcols) continue;
+    if (M * span <= (int)blockDim.x) {  // a single element
+      const int m = threadIdx.x / span, c = threadIdx.x % span, vc = c0 + c;
+      if (m >= M || vc >= nvcols) return;
       const long dst = a.dst_rows[m];
-      if (dst < 0 || dst >= a.cache_rows) continue;  // nowhere to write
+      if (dst < 0 || dst >= a.cache_rows) return;  // nowhere to write
       const int pos = a.positions[m];
       const bool bad = pos < 0 || pos >= a.pos_limit;
       const float *t = tile + m * ldt + c;
-      float o[8];
-      T *y;
-      if (one) {  // a single element
-        if (vc < kvd) {
-          const int h = vc / D, cc = vc % D;
-          const int pc = min(max(pos, 0), a.pos_limit - 1);
-          const float *rp = a.rope + ((size_t)pc * (D / 2) + 8 * (cc >> 4) + (cc & 7)) * 2;
-          const float pv = tile[m * ldt + (c ^ 8)];
-          const float v = bad ? qnan : ((cc & 8) ? (t[0] * rp[0] + pv * rp[1]) : (t[0] * rp[0] - pv * rp[1]));
-          ((T *)a.k_cache)[(size_t)dst * kvd + (size_t)h * D + rope_dim(cc, D)] = Elt<T>::from_f(v);
-        } else {
-          ((T *)a.v_cache)[(size_t)dst * kvd + (vc - kvd)] = Elt<T>::from_f(bad ? qnan : t[0]);
-        }
-        continue;
-      }
       if (vc < kvd) {
         const int h = vc / D, cc = vc % D;
         const int pc = min(max(pos, 0), a.pos_limit - 1);
-        // rotary pair index 8 (cc >> 4) + j of dims rope_dim(cc, D) + j
-        const float *rp = a.rope + ((size_t)pc * (D / 2) + 8 * (cc >> 4)) * 2;
-        float tv[8], pv[8];
-        tile8(t, ldt, tv);
-        tile8(tile + m * ldt + (c ^ 8), ldt, pv);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float cs = rp[2 * j], sn = rp[2 * j + 1];
-          o[j] = bad ? qnan : ((cc & 8) ? (tv[j] * cs + pv[j] * sn) : (tv[j] * cs - pv[j] * sn));
-        }
-        y = (T *)a.k_cache + (size_t)dst * kvd + (size_t)h * D + rope_dim(cc, D);
+        const float *rp = a.rope + ((size_t)pc * (D / 2) + 8 * (cc >> 4) + (cc & 7)) * 2;
+        const float pv = tile[m * ldt + (c ^ 8)];
+        const float v = bad ? qnan : ((cc & 8) ? (t[0] * rp[0] + pv * rp[1]) : (t[0] * rp[0] - pv * rp[1]));
+        ((T *)a.k_cache)[(size_t)dst * kvd + (size_t)h * D + rope_dim(cc, D)] = Elt<T>::from_f(v);
       } else {
-        tile8(t, ldt, o);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o[j] = bad ? qnan : o[j];
-        y = (T *)a.v_cache + (size_t)dst * kvd + (vc - kvd);
+        ((T *)a.v_cache)[(size_t)dst * kvd + (vc - kvd)] = Elt<T>::from_f(bad ? qnan : t[0]);
       }
-      if (aligned16(y)) {
-        store8<T>(y, o);
-      } else {
+      return;
+    }
+    // U groups at a time, first their rows' positions and destinations, then
+    // their rotary coefficients, then the stores: one chain of loads per U
+    // groups where a group by itself paid it each time
+    constexpr int U = 4;
+    const int gpr = span >> 3, n = M * gpr;
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * blockDim.x) {
+      int pos[U];
+      long dst[U];
+      f32x4 rp[U][4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) y[j] = Elt<T>::from_f(o[j]);
+      for (int u = 0; u < U; ++u) {
+        const int m = min(i0 + u * (int)blockDim.x, n - 1) / gpr;
+        pos[u] = a.positions[m];
+        dst[u] = a.dst_rows[m];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // rotary pair index 8 (cc >> 4) + j of dims rope_dim(cc, D) + j (value
+        // columns read the table too, and leave it)
+        const int vc = c0 + (min(i0 + u * (int)blockDim.x, n - 1) % gpr) * 8, cc = vc % D;
+        const int pc = min(max(pos[u], 0), a.pos_limit - 1);
+        const float *r = a.rope + ((size_t)pc * (D / 2) + 8 * (cc >> 4)) * 2;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) rp[u][w] = *reinterpret_cast<const f32x4 *>(r + 4 * w);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int idx = i0 + u * (int)blockDim.x;
+        if (idx >= n) break;
+        const int m = idx / gpr, c = (idx % gpr) * 8, vc = c0 + c;
+        if (vc >= nvcols || dst[u] < 0 || dst[u] >= a.cache_rows) continue;  // nowhere to write
+        const bool bad = pos[u] < 0 || pos[u] >= a.pos_limit;
+        const float *t = tile + m * ldt + c;
+        float o[8];
+        T *y;
+        if (vc < kvd) {
+          const int h = vc / D, cc = vc % D;
+          float tv[8], pv[8];
+          tile8(t, ldt, tv);
+          tile8(tile + m * ldt + (c ^ 8), ldt, pv);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const f32x4 w = rp[u][j >> 1];
+            const float cs = (j & 1) ? w.z : w.x, sn = (j & 1) ? w.w : w.y;
+            o[j] = bad ? qnan : ((cc & 8) ? (tv[j] * cs + pv[j] * sn) : (tv[j] * cs - pv[j] * sn));
+          }
+          y = (T *)a.k_cache + (size_t)dst[u] * kvd + (size_t)h * D + rope_dim(cc, D);
+        } else {
+          tile8(t, ldt, o);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) o[j] = bad ? qnan : o[j];
+          y = (T *)a.v_cache + (size_t)dst[u] * kvd + (vc - kvd);
+        }
+        if (aligned16(y)) {
+          store8<T>(y, o);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) y[j] = Elt<T>::from_f(o[j]);
+        }
       }
     }
   }
@@ -1229,6 +1378,45 @@ struct TileF32 {
       } else {
         for (int j = 0; j < 4 && c0 + c + j < nvcols; ++j) y[j] = t[j] + (rr ? rr[j] : 0.f);
       }
+    }
+  }
+};
+// Q/K/V projections of a prefill's rows in one launch (fp32, unrotated): the
+// rows of W_q, W_k, W_v as virtual columns, each projection's rows dense.
+// Four adjacent columns lie in one projection (head dims are multiples of 64).
+struct TileQkv {
+  static constexpr bool kRowStream = true, kSplitK = false, kSliced = true;
+  using Pre = NoPre;
+  __device__ Pre prefetch(int, int, int) const { return {}; }
+  static constexpr int kMidNtw = 0, kMidNtwMin = 1;
+  const bf16_t *w[3];
+  float *out[3];
+  int end[3];  // virtual columns below: W_q, then W_k, then W_v
+  int ldw, nvcols, lda;
+  __device__ const bf16_t *wrow(int c) const {
+    return c < end[0]   ? w[0] + (size_t)c * ldw
+           : c < end[1] ? w[1] + (size_t)(c - end[0]) * ldw
+                        : w[2] + (size_t)(c - end[1]) * ldw;
+  }
+  __device__ void slice(int z, int mrows, const bf16_t *&A, int &M) {
+    const int m0 = z * mrows;
+    A += (size_t)m0 * lda;
+    M = min(mrows, M - m0);
+    out[0] += (size_t)m0 * end[0];
+    out[1] += (size_t)m0 * (end[1] - end[0]);
+    out[2] += (size_t)m0 * (end[2] - end[1]);
+  }
+  __device__ void finish(float *tile, int ldt, int M, int c0, int span, const Pre &) const {
+    const int gpr = span >> 2;
+    for (int idx = threadIdx.x; idx < M * gpr; idx += blockDim.x) {
+      const int m = idx / gpr, c = (idx % gpr) * 4, vc = c0 + c;
+      if (vc >= nvcols) continue;
+      const float *t = tile + m * ldt + c;
+      float *y = vc < end[0]   ? out[0] + (size_t)m * end[0] + vc
+                 : vc < end[1] ? out[1] + (size_t)m * (end[1] - end[0]) + vc - end[0]
+                               : out[2] + (size_t)m * (end[2] - end[1]) + vc - end[1];
+      *reinterpret_cast<f32x4 *>(y) =
+          (ldt & 3) == 0 ? *reinterpret_cast<const f32x4 *>(t) : f32x4{t[0], t[1], t[2], t[3]};
     }
   }
 };
@@ -1621,10 +1809,10 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
       if ((size_t)ksb * M * ldpb <= ss->floats) {
         if (M > 128)
           hipLaunchKernelGGL((k_gemm_tile<4, 4, 4, 2, 3, Epi, true>), dim3(gx, ksb, 1), dim3(512), 0, s,
-                             A, lda, arows, M, K, epi, ss->p, ldpb);
+                             A, lda, arows, M, K, epi, ss->p, ldpb, 1);
         else  // 128 x 128 tiles
           hipLaunchKernelGGL((k_gemm_tile<4, 2, 2, 4, 3, Epi, true>), dim3(gx, ksb, 1), dim3(512), 0, s,
-                             A, lda, arows, M, K, epi, ss->p, ldpb);
+                             A, lda, arows, M, K, epi, ss->p, ldpb, 1);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || so) {  // the caller sums the slices
           if (so) *so = SplitOut{ss->p, ldpb, ksb};
@@ -1721,6 +1909,22 @@ hipError_t gemm_store(int dt, const void *A, int lda, int M, int K, const void *
   return run_gemm<float, 1, 8, 1>((const float *)A, lda, kDenseRows, M, K, e, nullptr, s, ss);
 }
 
+// The row pass of a residual GEMM: sums its slices (so.ks > 0; else out already
+// holds the rows), adds the residual, stores the rows and writes their
+// normalised copies (none: the rows alone).
+template <typename T>
+static hipError_t resid_rows(const SplitOut &so, int M, int ncols, const float *resid, long ldr,
+                             float *out, long ldo, const GainCopies &gains, float eps, hipStream_t s) {
+  if (so.ks == 0 && gains.n == 0) return hipSuccess;
+#define FE_RROWS(NVV)                                                                            \
+  hipLaunchKernelGGL((k_resid_rows<T, NVV>), dim3(M), dim3(kRowThreads), 0, s, so.p, so.ldp,      \
+                     so.ks, M, ncols, resid, ldr, out, ldo, gains, eps)
+  if (ncols <= 4 * kRowThreads) FE_RROWS(1);
+  else FE_RROWS(2);
+#undef FE_RROWS
+  return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t resid_norm_rows(const T *A, int lda, int M, int K, const T *W, int ncols,
                                   float *out, long ldo, const float *resid, long ldr,
@@ -1732,13 +1936,7 @@ static hipError_t resid_norm_rows(const T *A, int lda, int M, int K, const T *W,
   SplitOut so;
   const hipError_t ge = run_gemm<T, 1, 8, 1>(A, lda, kDenseRows, M, K, e, nullptr, s, ss, &so);
   if (ge != hipSuccess) return ge;
-#define FE_RROWS(NVV)                                                                            \
-  hipLaunchKernelGGL((k_resid_rows<T, NVV>), dim3(M), dim3(kRowThreads), 0, s, so.p, so.ldp,      \
-                     so.ks, M, ncols, resid, ldr, out, ldo, gains, eps)
-  if (ncols <= 4 * kRowThreads) FE_RROWS(1);
-  else FE_RROWS(2);
-#undef FE_RROWS
-  return hipGetLastError();
+  return resid_rows<T>(so, M, ncols, resid, ldr, out, ldo, gains, eps, s);
 }
 
 hipError_t gemm_resid(int dt, const void *A, int lda, int M, int K, const void *W, int ncols,
@@ -1785,27 +1983,52 @@ hipError_t gemm_kvcache(int dt, const void *A, int lda, int M, const KvCacheArgs
   return run_gemm<float, 1, 8, 1>((const float *)A, lda, kDenseRows, M, a.d, e, nullptr, s, ss);
 }
 
-// Many rows at once (bf16): 128 x 128 output tiles of k_gemm_tile (K a
-// multiple of 64; else k_gemm_mid's 128 x 64 tiles), grid z over 128-row
-// blocks (and layers), no split of K.
+// Many rows at once (bf16).  K a multiple of 64: k_gemm_tile in the shape
+// pick_tile finds, K split into slices where a row kernel can sum them; else
+// k_gemm_mid's 128 x 64 tiles.  grid z covers the row blocks (and layers).
 constexpr int kTileNtw = 2, kTileWn = 2, kTileStages = 3, kTileRows = 64 * (4 / kTileWn),
               kTileCols = 16 * kTileNtw * kTileWn;
-static_assert(kTileRows == kBigRows, "both tiled kernels slice 128-row blocks (TileKv's nblocks)");
+
+template <class Epi>
+static hipError_t rows_unsplit(const bf16_t *A, int lda, int M, int K, const Epi &e, hipStream_t s) {
+  if (K % 64 == 0)
+    return launch_tile<Epi, false>(pick_tile(M, e.nvcols, K, 1, 1), A, lda, M, K, e, 1, nullptr, 0, s);
+  const dim3 grid((e.nvcols + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
+  hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, Epi>), grid, dim3(256), 0, s,
+                     A, lda, kDenseRows, M, K, e, nullptr, 0);
+  return hipGetLastError();
+}
+// slices of M rows x ncols columns (padded to the tile) that the scratch holds
+static int rows_max_slices(const SplitScratch *ss, int M, int ncols) {
+  if (!ss || !ss->p) return 1;
+  const size_t n = ss->floats / ((size_t)M * ((ncols + 255) / 256 * 256));
+  return n < 1 ? 1 : (int)(n < (size_t)kMaxSlices ? n : kMaxSlices);
+}
 
 hipError_t gemm_store_rows(const void *A, int lda, int M, int K, const void *W, int ncols, void *out,
                            int ldo, const void *embed, const int32_t *tokens, int vocab,
-                           void *gather_out, int ld_gather, int d, hipStream_t s) {
+                           void *gather_out, int ld_gather, int d, hipStream_t s,
+                           const SplitScratch *ss) {
   if (M <= 0) return hipSuccess;
   TileStore e;
   static_cast<EpiStore<bf16_t> &>(e) = EpiStore<bf16_t>{(const bf16_t *)W, K, ncols, (bf16_t *)out,
                                                         ldo, (const bf16_t *)embed, tokens, vocab,
                                                         (bf16_t *)gather_out, ld_gather, d, M};
   e.lda = lda;
-  if (K % 64 == 0) return launch_tile((const bf16_t *)A, lda, M, K, e, ncols, (M + kBigRows - 1) / kBigRows, s);
-  const dim3 grid((ncols + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
-  hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, TileStore>), grid, dim3(256),
-                     0, s, (const bf16_t *)A, lda, kDenseRows, M, K, e, nullptr, 0);
-  return hipGetLastError();
+  if (K % 64 == 0 && ncols % 8 == 0) {
+    const TilePick p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
+    if (p.ks > 1) {
+      const int ldp = (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape];
+      const hipError_t err = launch_tile<EpiStore<bf16_t>, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
+                                                                 ss->p, ldp, s);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(k_store_rows, dim3(M), dim3(256), 0, s, (const float *)ss->p, ldp, p.ks, M,
+                         ncols, (bf16_t *)out, ldo, (const bf16_t *)embed, tokens, vocab,
+                         (bf16_t *)gather_out, ld_gather, d);
+      return hipGetLastError();
+    }
+  }
+  return rows_unsplit((const bf16_t *)A, lda, M, K, e, s);
 }
 
 hipError_t gemm_swiglu_rows(const void *A, int lda, int M, int K, const void *w_gate,
@@ -1815,24 +2038,40 @@ hipError_t gemm_swiglu_rows(const void *A, int lda, int M, int K, const void *w_
   static_cast<EpiSwiglu<bf16_t> &>(e) = EpiSwiglu<bf16_t>{(const bf16_t *)w_gate, (const bf16_t *)w_up,
                                                           K, I, 2 * I, (bf16_t *)out, ldo};
   e.lda = lda;
-  if (K % 64 == 0) return launch_tile((const bf16_t *)A, lda, M, K, e, 2 * I, (M + kBigRows - 1) / kBigRows, s);
-  const dim3 grid((2 * I + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
-  hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, TileSwiglu>), grid,
-                     dim3(256), 0, s, (const bf16_t *)A, lda, kDenseRows, M, K, e, nullptr, 0);
-  return hipGetLastError();
+  return rows_unsplit((const bf16_t *)A, lda, M, K, e, s);
 }
 
 hipError_t gemm_resid_rows(const void *A, int lda, int M, int K, const void *W, int ncols, float *out,
-                           long ldo, hipStream_t s, const float *resid, long ldr) {
+                           long ldo, hipStream_t s, const float *resid, long ldr,
+                           const GainCopies &norms, float eps, const SplitScratch *ss) {
   if (M <= 0) return hipSuccess;
-  TileF32 e{(const bf16_t *)W, K, ncols, out, ldo, lda};
-  e.resid = resid;
-  e.ldr = ldr;
-  if (K % 64 == 0) return launch_tile((const bf16_t *)A, lda, M, K, e, ncols, (M + kBigRows - 1) / kBigRows, s);
-  const dim3 grid((ncols + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
-  hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, TileF32>), grid, dim3(256),
-                     0, s, (const bf16_t *)A, lda, kDenseRows, M, K, e, nullptr, 0);
-  return hipGetLastError();
+  if (ncols > 8192 || ncols % 4) return hipErrorInvalidValue;
+  SplitOut so;
+  TilePick p{kTile128x128, 1};
+  if (K % 64 == 0) p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
+  if (p.ks > 1) {
+    const EpiResid<bf16_t> e{(const bf16_t *)W, K, ncols, out, ldo, resid, ldr, nullptr, 1, 0, GainCopies{}};
+    so = SplitOut{ss->p, (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape], p.ks};
+    const hipError_t err = launch_tile<EpiResid<bf16_t>, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
+                                                               ss->p, so.ldp, s);
+    if (err != hipSuccess) return err;
+  } else {
+    TileF32 e{(const bf16_t *)W, K, ncols, out, ldo, lda};
+    e.resid = resid;
+    e.ldr = ldr;
+    const hipError_t err = rows_unsplit((const bf16_t *)A, lda, M, K, e, s);
+    if (err != hipSuccess) return err;
+  }
+  return resid_rows<bf16_t>(so, M, ncols, resid, ldr, out, ldo, norms, eps, s);
+}
+
+hipError_t gemm_qkv_rows(const void *A, int lda, int M, int K, const void *wq, const void *wk,
+                         const void *wv, int qd, int kvd, float *q, float *k, float *v,
+                         hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  const TileQkv e{{(const bf16_t *)wq, (const bf16_t *)wk, (const bf16_t *)wv}, {q, k, v},
+                  {qd, qd + kvd, qd + 2 * kvd}, K, qd + 2 * kvd, lda};
+  return rows_unsplit((const bf16_t *)A, lda, M, K, e, s);
 }
 
 hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int nlayers,
@@ -1869,8 +2108,11 @@ hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int 
                        (const bf16_t *)A, lda, kDenseRows, M, layers[0].d, e, nullptr, 0);
     return hipGetLastError();
   }
-  if (layers[0].d % 64 == 0)
-    return launch_tile((const bf16_t *)A, lda, M, layers[0].d, e, e.nvcols, e.g.nblocks * nlayers, s);
+  if (layers[0].d % 64 == 0) {
+    const TilePick p = pick_tile(M, e.nvcols, layers[0].d, nlayers, 1);
+    e.g.nblocks = (M + kTileM[p.shape] - 1) / kTileM[p.shape];
+    return launch_tile<TileKv, false>(p, (const bf16_t *)A, lda, M, layers[0].d, e, nlayers, nullptr, 0, s);
+  }
   const dim3 grid((e.nvcols + kTileCols - 1) / kTileCols, 1, e.g.nblocks * nlayers);
   hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, TileKv>), grid, dim3(256), 0,
                      s, (const bf16_t *)A, lda, kDenseRows, M, layers[0].d, e, nullptr, 0);
@@ -1906,7 +2148,7 @@ hipError_t gemm_lmhead(int dt, const void *A, int lda, const ARows &arows, int M
     const int gx = (a.V + 127) / 128;
     *nwg_out = gx;
     hipLaunchKernelGGL((k_gemm_tile<4, 4, 4, 2, 3, EpiLm<bf16_t>>), dim3(gx), dim3(512), 0, s,
-                       (const bf16_t *)A, lda, arows, M, K, e, nullptr, 0);
+                       (const bf16_t *)A, lda, arows, M, K, e, nullptr, 0, 1);
     return hipGetLastError();
   }
   if (dt) {

@@ -367,21 +367,28 @@ struct KvCacheArgs {
 hipError_t gemm_kvcache(int dt, const void *A, int lda, int M, const KvCacheArgs &a,
                         hipStream_t s, const SplitScratch *ss = nullptr);
 
-// Many-row bf16 GEMMs of the cache update: 128 x 64 output tiles over a 2-D
-// grid (row blocks in grid z), K unsplit.  gemm_store_rows / gemm_resid_rows
-// behave as gemm_store / gemm_resid (no residual, sums of squares or gain
-// copies).
+// Many-row bf16 GEMMs of the cache update and the prefill, over a 2-D grid of
+// output tiles (row blocks in grid z), K split into slices where ss holds them
+// and that pays.  gemm_store_rows behaves as gemm_store; gemm_resid_rows gives
+// fp32 rows out = (resid +) A W^T and, with norms.n > 0, their RMS-normalised
+// copies gamma_q * out / rms(out); gemm_qkv_rows the three projections' rows,
+// dense and unrotated.
 hipError_t gemm_store_rows(const void *A, int lda, int M, int K, const void *W, int ncols, void *out,
                            int ldo, const void *embed, const int32_t *tokens, int vocab,
-                           void *gather_out, int ld_gather, int d, hipStream_t s);
+                           void *gather_out, int ld_gather, int d, hipStream_t s,
+                           const SplitScratch *ss);
 hipError_t gemm_resid_rows(const void *A, int lda, int M, int K, const void *W, int ncols, float *out,
-                           long ldo, hipStream_t s, const float *resid = nullptr, long ldr = 0);
+                           long ldo, hipStream_t s, const float *resid, long ldr,
+                           const GainCopies &norms, float eps, const SplitScratch *ss);
+hipError_t gemm_qkv_rows(const void *A, int lda, int M, int K, const void *wq, const void *wk,
+                         const void *wv, int qd, int kvd, float *q, float *k, float *v,
+                         hipStream_t s);
 hipError_t gemm_swiglu_rows(const void *A, int lda, int M, int K, const void *w_gate,
                             const void *w_up, int I, void *out, int ldo, hipStream_t s);
 // Every layer's K/V projection into its cache in one launch (bf16): layer l's
 // normalised rows at A + l * a_layer_stride.  With na (M <= 16) A holds
 // gamma * x per layer and the rows' 1/rms come from na's sums of squares;
-// otherwise 128-row tiles (32 columns wide below 128 rows, 64 from there on).
+// otherwise tiles of 128 or 256 rows (32 columns wide below 128 rows).
 hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int nlayers,
                         const KvCacheArgs *layers, const NormA *na, hipStream_t s);
 

@@ -1129,7 +1129,17 @@ extern "C" size_t fe_kv_update_workspace_bytes(const fe_config *cfg, int32_t chu
 // context): x_0 of every row as in the pass (Eq. 1), then per layer its
 // RMSNorm and the rotated K / V projections, scattered into the caches.
 namespace {
-// The N layers over Mc new rows of the self context, whose x_0 rows are in U.X:
+GainCopies one_norm(const void *gamma, void *dst, long ld) {
+  GainCopies gc{};
+  gc.n = 1;
+  gc.gamma[0] = gamma;
+  gc.dst[0] = dst;
+  gc.ld[0] = ld;
+  return gc;
+}
+
+// The N layers over Mc new rows of the self context, whose x_0 rows are in U.X
+// (at kTiledRows rows and more, bf16, also normalised for the first layer in U.an):
 // layer by layer, every row's Q/K/V, its K/V into the cache, then its attention
 // over its sequence's rows of earlier positions (the rows this step just wrote
 // included) plus its own key, the O projection, the MLP, x_i into U.X.  Rows
@@ -1162,7 +1172,7 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
   for (int l = 0; l < c.n_layers; ++l) {
     const Range range("fe.prefill_layer");
     const fe_layer_weights &lw = h->layers[l];
-    FE_TRY(rmsnorm_rows(dt, X, Mc, 1, 0, d, 0, lw.attn_norm, an, d, c.rms_eps, s));
+    if (!tiled) FE_TRY(rmsnorm_rows(dt, X, Mc, 1, 0, d, 0, lw.attn_norm, an, d, c.rms_eps, s));
     if (l + 1 == c.n_layers) {
       // the last layer only keys its input: nothing reads its output state, so
       // its queries, attention and MLP are not run
@@ -1180,12 +1190,8 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
       }
       break;
     }
-    if (tiled) {
-      // q, K, V of every row (fp32, unrotated: the attention rotates them)
-      FE_TRY(gemm_resid_rows(an, d, Mc, d, lw.wq, qd, q, qd, s));
-      FE_TRY(gemm_resid_rows(an, d, Mc, d, lw.wk, kvd, knew, kvd, s));
-      FE_TRY(gemm_resid_rows(an, d, Mc, d, lw.wv, kvd, vnew, kvd, s));
-    }
+    if (tiled)  // q, K, V of every row (fp32, unrotated: the attention rotates them)
+      FE_TRY(gemm_qkv_rows(an, d, Mc, d, lw.wq, lw.wk, lw.wv, qd, kvd, q, knew, vnew, s));
     for (int s0 = 0; s0 < Mc && !tiled; s0 += kGemmMaxRows) {
       const int Ms = std::min(kGemmMaxRows, Mc - s0);
       const QkvArgs qa{lw.wq, lw.wk, lw.wv, d, D, Hq, Hkv, 1, 0, 0, Seqs{ranges + 2 * s0, 1},
@@ -1207,19 +1213,20 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
                        part, nch, U.nch_ld, cpw, ao + (size_t)s0 * qd * es, Ms, Hq, Hkv, D, rope,
                        0, pmax, s));
     }
-    if (tiled) {  // x' = x_{i-1} + W_o o
-      FE_TRY(gemm_resid_rows(ao, qd, Mc, qd, lw.wo, d, Xp, d, s, X, d));
-    }
+    if (tiled)  // x' = x_{i-1} + W_o o and its normalised rows
+      FE_TRY(gemm_resid_rows(ao, qd, Mc, qd, lw.wo, d, Xp, d, s, X, d, one_norm(lw.mlp_norm, an, d),
+                             c.rms_eps, ss));
     for (int s0 = 0; s0 < Mc && !tiled; s0 += kGemmMaxRows) {
       const int Ms = std::min(kGemmMaxRows, Mc - s0);
       // x' = x_{i-1} + W_o o
       FE_TRY(gemm_resid(dt, ao + (size_t)s0 * qd * es, qd, Ms, qd, lw.wo, d, Xp + (size_t)s0 * d,
                         d, X + (size_t)s0 * d, d, nullptr, 1, 0, nullptr, s, ss));
     }
-    FE_TRY(rmsnorm_rows(dt, Xp, Mc, 1, 0, d, 0, lw.mlp_norm, an, d, c.rms_eps, s));
-    if (tiled) {  // SwiGLU rows, then x_i = x' + W_d s (Eq. 2)
+    if (!tiled) FE_TRY(rmsnorm_rows(dt, Xp, Mc, 1, 0, d, 0, lw.mlp_norm, an, d, c.rms_eps, s));
+    if (tiled) {  // SwiGLU rows, then x_i = x' + W_d s (Eq. 2), normalised for the next layer
       FE_TRY(gemm_swiglu_rows(an, d, Mc, d, lw.w_gate, lw.w_up, I, sb, I, s));
-      FE_TRY(gemm_resid_rows(sb, I, Mc, I, lw.w_down, d, X, d, s, Xp, d));
+      FE_TRY(gemm_resid_rows(sb, I, Mc, I, lw.w_down, d, X, d, s, Xp, d,
+                             one_norm(h->layers[l + 1].attn_norm, an, d), c.rms_eps, ss));
     }
     for (int s0 = 0; s0 < Mc && !tiled; s0 += kGemmMaxRows) {
       const int Ms = std::min(kGemmMaxRows, Mc - s0);
@@ -1316,12 +1323,20 @@ fe_status kv_update_impl(fe_drafter *h, int32_t n_rows, const void *features,
       continue;
     }
     if (dt && Mc >= kTiledRows) {
-      // many rows: one launch per stage over 128 x 64 output tiles
+      // many rows: one launch per stage over 2-D tiles
       // (matrix-core bound from a few hundred rows)
       FE_TRY(gemm_store_rows((const char *)features + (size_t)r0 * F * d * es, F * d, Mc, F * d,
                              h->w.w_fuse, d, cat, 2 * d, h->w.embed, tokens + r0, c.target_vocab,
-                             cat + (size_t)d * es, 2 * d, d, s));
-      FE_TRY(gemm_resid_rows(cat, 2 * d, Mc, 2 * d, h->w.w_in, d, X, d, s));
+                             cat + (size_t)d * es, 2 * d, d, s, &ss));
+      // x_0 and its normalised rows for every layer (self context: the first)
+      GainCopies gc{};
+      gc.n = self ? 1 : c.n_layers;
+      for (int l = 0; l < gc.n; ++l) {
+        gc.gamma[l] = h->layers[l].attn_norm;
+        gc.dst[l] = an + (size_t)l * C * d * es;
+        gc.ld[l] = d;
+      }
+      FE_TRY(gemm_resid_rows(cat, 2 * d, Mc, 2 * d, h->w.w_in, d, X, d, s, nullptr, 0, gc, c.rms_eps, &ss));
     } else {
       // stage by stage over the chunk, so that each weight matrix is read by
       // consecutive launches
@@ -1345,13 +1360,15 @@ fe_status kv_update_impl(fe_drafter *h, int32_t n_rows, const void *features,
     }
     if (dt) {
       // every layer's normalised rows from one RMS per row (one launch)
-      RmsCopies rc{};
-      rc.n = c.n_layers;
-      for (int l = 0; l < c.n_layers; ++l) {
-        rc.gamma[l] = h->layers[l].attn_norm;
-        rc.out[l] = an + (size_t)l * C * d * es;
+      if (Mc < kTiledRows) {
+        RmsCopies rc{};
+        rc.n = c.n_layers;
+        for (int l = 0; l < c.n_layers; ++l) {
+          rc.gamma[l] = h->layers[l].attn_norm;
+          rc.out[l] = an + (size_t)l * C * d * es;
+        }
+        FE_TRY(rmsnorm_copies(dt, X, Mc, rc, d, c.rms_eps, s));
       }
-      FE_TRY(rmsnorm_copies(dt, X, Mc, rc, d, c.rms_eps, s));
       KvCacheArgs la[kMaxLayers];
       layer_args(r0, la);
       FE_TRY(gemm_kv_rows(an, d, (long)C * d, Mc, c.n_layers, la, nullptr, s));

@@ -78,3 +78,25 @@ def test_tiles_keep_nan_rows_apart():
         assert_rows_close(f"array {i}", a[ok], b[ok], TOL["bf16"])
     last = np.isnan(tiles[cfg.n_layers - 1][up.dst_rows]).any(1)  # the deepest layer's keys
     assert last[50:80].all() and last[3] and not last[:3].any() and not last[80:].any()
+
+
+# MLP widths whose gate/up GEMM (512 wide K) takes each tile shape at 300 rows:
+# 128 x 128, 128 x 192, 128 x 256, 256 x 224 and 256 x 256, with a ragged last
+# row block and last column tile; the fusion and down FCs (K above 1024) run as
+# summed K slices, 1088 wide also the down FC with a ragged share of chunks
+@pytest.mark.parametrize("inter", [1088, 6016, 9056, 12000, 29984])
+def test_tile_shapes_match_oracle(inter):
+    from tests.test_gpu_kv_update_self import _run
+    cfg = SELF(C.SMALL_GQA_BF16).with_(intermediate=inter, n_layers=2)
+    up = make_update_rows(cfg, np.array([290, 10]), np.array([0, 3]), capacity=290, seed=13)
+    _run(cfg, up, 1024, max_prefix=290)
+
+
+@pytest.mark.parametrize("layers", [5, 7])
+def test_cascade_rows_over_tiles_match_oracle(layers):
+    """Every layer's K/V rows in one launch of 256 x 224 (5 layers) and
+    256 x 256 (7) tiles."""
+    from tests.test_gpu_kv_update import _run
+    cfg = C.SMALL_MHA_BF16_D128.with_(n_q_heads=16, n_kv_heads=16, n_layers=layers, name="wide_kv")
+    up = make_update_rows(cfg, np.array([400, 77]), np.array([0, 5]), capacity=400, seed=14)
+    _run(cfg, up, 1024)
