@@ -421,16 +421,21 @@ hipError_t accept_greedy(int B, int N, int k, const int32_t *tokens, const int32
 // target id keeps p(x) in memory; an LDS bitmask marks the mapped target ids.
 // Sampled children are tested in draw order (their Gumbel keys, recomputed
 // from the drafting uniforms) by recursive rejection sampling (accept when
-// u * q_i(x) <= r(x) / Z; on a rejection rd <- (rd - Z q_i)^+ and x leaves q),
-// unsampled ones in listing order against point masses (accept when
-// u <= r(x) / Z, else rd(x) <- 0).  The last uniform draws one token by
+// u * q_i(x) <= r(x) / Z; on a rejection r <- (r - Z q_i)^+ and x leaves q)
+// (one growing multiple of q, in registers), unsampled ones in listing order
+// against point masses (accept when u <= r(x) / Z, else rd(x) <- 0).  The last uniform draws one token by
 // inverse CDF: mapped ids first in draft-id order, then the other target ids
 // in increasing order.  Each wave owns a contiguous chunk of the ids and
 // reads it 64 consecutive ids per step (coalesced): one pass per visited node
 // sums p (Z) and the unmapped part of every chunk; chunk sums are added in
 // order, the chunks' ranges tile the line exactly, and the owning wave walks
 // its chunk with wave scans to the drawn id.  Loads are issued kAccBatch at a
-// time.  Every decision is taken on block-reduced values, so control flow is
+// time.  Bound by the dependent passes of one CU, so by the instructions a pass
+// issues per id: a row pass tests a lane's four ids against one mask word and
+// adds the unmapped ones only (Z adds the gathered mapped values), a rejection
+// rewrites nothing (8 sequences at the 8B vocabularies: 93 us with a sum, a
+// mask test and a last-id update per id and a rewritten residual, 73 so).
+// Every decision is taken on block-reduced values, so control flow is
 // uniform across the workgroup.
 // ---------------------------------------------------------------------------
 constexpr int kAccThreads = 1024;
@@ -536,17 +541,14 @@ __host__ __device__ inline int acc_chunk_width(int Vt, int W) {
 // Few sequences: before the walk, every node's target row is reduced by
 // workgroups of its own instead of by the one walking workgroup when (and if)
 // it gets there.  Row (sequence b, node n), workgroup y < kAccWaves: chunk y's
-// sum of p, its unmapped part (ids no draft id maps to) and its last unmapped
-// id with mass; y >= kAccWaves: p at the mapped ids of draft ids
+// sum of p and its unmapped part (ids no draft id maps to); y >= kAccWaves: p at the mapped ids of draft ids
 // [(y - kAccWaves) * VP, ...) (the walk's residual row, compact).
 constexpr int kAccPreThreads = 256, kAccPreGather = 16;
 template <int W>
 __global__ __launch_bounds__(kAccPreThreads) void k_accept_rows(
     int Vt, int V, const int32_t *__restrict__ d2t, const float *__restrict__ target_probs,
-    const uint32_t *__restrict__ img, float *__restrict__ agg, int32_t *__restrict__ agg_last,
-    float *__restrict__ gathered) {
+    const uint32_t *__restrict__ img, float *__restrict__ agg, float *__restrict__ gathered) {
   __shared__ float red[kAccPreThreads / 64];
-  __shared__ int redi[kAccPreThreads / 64];
   const int row = blockIdx.x, y = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float *p = target_probs + (size_t)row * Vt;
   if (y >= kAccWaves) {
@@ -561,7 +563,6 @@ __global__ __launch_bounds__(kAccPreThreads) void k_accept_rows(
   const int CW = acc_chunk_width(Vt, W);
   const int c0 = min(y * CW, Vt), c1 = min(c0 + CW, Vt);
   float zs = 0.f, cn = 0.f;
-  int last = -1;
   for (int x0 = c0 + tid * W; x0 < c1; x0 += kAccPreThreads * W) {
     float a[W];
     if constexpr (W == 4) {
@@ -575,29 +576,17 @@ __global__ __launch_bounds__(kAccPreThreads) void k_accept_rows(
       const int x = x0 + q;
       if (x >= c1) continue;
       zs += a[q];
-      if (!((img[x >> 5] >> (x & 31)) & 1u)) {
-        cn += a[q];
-        if (a[q] > 0.f) last = x;
-      }
+      if (!((img[x >> 5] >> (x & 31)) & 1u)) cn += a[q];
     }
   }
   zs = group_sum<64>(zs);
   cn = group_sum<64>(cn);
-  last = (int)group_max<64>((float)last);
-  if (lane == 0) {
-    red[wave] = zs;
-    redi[wave] = last;
-  }
+  if (lane == 0) red[wave] = zs;
   __syncthreads();
   if (tid == 0) {
     float z = 0.f;
-    int l = -1;
-    for (int w = 0; w < kAccPreThreads / 64; ++w) {
-      z += red[w];
-      l = max(l, redi[w]);
-    }
+    for (int w = 0; w < kAccPreThreads / 64; ++w) z += red[w];
     agg[((size_t)row * kAccWaves + y) * 2] = z;
-    agg_last[(size_t)row * kAccWaves + y] = l;
   }
   __syncthreads();
   if (lane == 0) red[wave] = cn;
@@ -610,7 +599,7 @@ __global__ __launch_bounds__(kAccPreThreads) void k_accept_rows(
 }
 
 // VEC: target rows read four ids per lane (Vt % 4 == 0, 16-byte aligned rows).
-// agg / agg_last / gathered (k_accept_rows, or null): the nodes' rows reduced
+// agg / gathered (k_accept_rows, or null): the nodes' rows reduced
 // beforehand; the walk then reads them instead of the target rows.
 template <bool VEC>
 __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
@@ -620,8 +609,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
     Draws draft_draws, const int32_t *__restrict__ d2t,
     const float *__restrict__ target_probs, const float *__restrict__ uniforms,
     const uint32_t *__restrict__ img, int32_t *accept_len, int32_t *accept_path,
-    int32_t *accepted, const float *__restrict__ agg, const int32_t *__restrict__ agg_last,
-    const float *__restrict__ gathered) {
+    int32_t *accepted, const float *__restrict__ agg, const float *__restrict__ gathered) {
   constexpr int W = VEC ? 4 : 1;  // target ids per lane per load
   __shared__ float s_rd[kAccMaxV];
   __shared__ uint32_t s_img[kAccMaxVt / 32];
@@ -660,7 +648,6 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
   const int c0 = min(wave * CW, Vt), c1 = min(c0 + CW, Vt);
   int node = 0, len = 0, t = 0;
   float Z = 0.f;
-  int lastn = -1;  // last unmapped id with mass in this lane's share of the chunk
   const float *p = target_probs + (size_t)b * T * Vt;
   // loads W consecutive target ids at x of row p (zeros past the chunk)
   auto loadp = [&](int x, float *a) {
@@ -679,15 +666,15 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
     const int lvl = len + 1;
     const size_t lrow = (size_t)b * N + (lvl - 1);
     const int cdv = (tid < k && lvl <= N) ? topk_draft[lrow * k + tid] : 0;
+    const bool has_children = lvl <= N && (node == 0 || node == 1 + (lvl - 2) * k);
+    // Z is the unmapped part (cn, this pass) plus p at the mapped ids (gathered below)
     float zs = 0.f, cn = 0.f;
-    lastn = -1;
     constexpr int NB = kAccBatch / W;
     if (agg) {  // reduced beforehand: chunk sums (summed in chunk order) and rd
       const size_t r = (size_t)b * T + node;
       float z = 0.f;
       for (int w = 0; w < kAccWaves; ++w) z += agg[(r * kAccWaves + w) * 2];
       if (lane == 0) s_cn[wave] = agg[(r * kAccWaves + wave) * 2 + 1];
-      lastn = agg_last[r * kAccWaves + wave];
       for (int v = tid; v < V; v += kAccThreads) s_rd[v] = gathered[r * V + v];
       __syncthreads();
       Z = z;
@@ -699,19 +686,19 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
       for (int j = 0; j < NB; ++j) loadp(e + 64 * W * j + W * lane, a[j]);
 #pragma unroll
       for (int j = 0; j < NB; ++j)
+      {
+        // the ids' bits of the mask (W aligned ids lie in one word); ids past
+        // the chunk were read as zeros
+        const int x = e + 64 * W * j + W * lane;
+        const uint32_t bits = s_img[min(x, Vt - 1) >> 5] >> (x & 31);
 #pragma unroll
-        for (int q = 0; q < W; ++q) {
-          const int x = e + 64 * W * j + W * lane + q;
-          zs += a[j][q];
-          if (x < c1 && !in_img(x)) {
-            cn += a[j][q];
-            if (a[j][q] > 0.f) lastn = x;
-          }
-        }
+        for (int q = 0; q < W; ++q) cn += (bits >> q) & 1u ? 0.f : a[j][q];
+      }
     }
     if (!agg) {
-    cn = group_sum<64>(cn);
-    if (lane == 0) s_cn[wave] = cn;  // read after the barriers below
+      zs = cn;
+      cn = group_sum<64>(cn);
+      if (lane == 0) s_cn[wave] = cn;  // read after the barriers below
     }
     // rd = p at the mapped ids: the map, then the values, half the ids at a time
 #pragma unroll 1
@@ -730,10 +717,10 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
       for (int j = 0; j < kZ / 2; ++j) {
         const int v = tid + (h + j) * kAccThreads;
         if (v < V) s_rd[v] = g[j];
+        zs += g[j];
       }
     }
     if (!agg) Z = acc_sum(zs, red);  // its barriers also publish s_rd
-    const bool has_children = lvl <= N && (node == 0 || node == 1 + (lvl - 2) * k);
     if (!has_children) break;
     const float *z = draft_logits + lrow * V;
     // the children: draft ids, tempered logits, keys and the uniforms of the
@@ -784,17 +771,23 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
     }
     const float S = acc_sum(se, red);
     float R = 0.f;  // q mass of the rejected children
+    // The residual after rejections is (p - C q)^+ with one growing C: each
+    // one subtracts a multiple of q and clips at 0, and clipping in between or
+    // at the end is the same.  So s_rd keeps p until the last child is
+    // rejected, and a rejection is one sum of min(p, C q), the mass that has
+    // gone.  (C counts in units of exp(z / T - mx).)
+    float C = 0.f;
+    const float Z0 = Z;
     bool took = false;
     for (int j = 0; j < k; ++j) {
       const int rho = s_ord[j];
       const int child = 1 + (lvl - 1) * k + rho;
       const int vd = s_cd[rho];
-      const float q0v = expf(s_zc[rho] - mx) / S;
+      const float e0v = expf(s_zc[rho] - mx), q0v = e0v / S;
       const float qi = draft_draws.on() ? q0v / (1.f - R) : 1.f;
-      const float rx = s_rd[vd];
+      const float rx = draft_draws.on() ? fmaxf(s_rd[vd] - C * e0v, 0.f) : s_rd[vd];
       const float ut = s_uc[j];
       ++t;
-      __syncthreads();  // every thread has read rd(x) before it changes
       if (ut * qi <= rx / Z) {
         node = child;
         ++len;
@@ -803,29 +796,38 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
         break;
       }
       if (!draft_draws.on()) {  // point mass on x: x leaves p
+        __syncthreads();  // every thread has read rd(x) before it changes
         if (tid == 0) s_rd[vd] = 0.f;
         Z -= rx;
         __syncthreads();
         continue;
       }
-      // rd <- (rd - Z q_i)^+.  A rejected x had r(x) / Z < q_i(x), so its rd
-      // is now 0 and stays 0 in later passes: leaving x out of q changes
-      // nothing further but the renormalisation 1 / (1 - R).
-      const float scale = Z / (1.f - R);
+      // r <- (r - Z q_i)^+.  A rejected x had r(x) / Z < q_i(x), so its r is
+      // now 0 and stays 0 as C grows: leaving x out of q changes nothing
+      // further but the renormalisation 1 / (1 - R).
+      C += Z / (1.f - R) / S;
       float dec = 0.f;
 #pragma unroll
       for (int jj = 0; jj < kZ; ++jj) {
         const int v = tid + jj * kAccThreads;
-        if (v >= V) continue;
-        const float old = s_rd[v];
-        const float nr = fmaxf(old - scale * (zr[jj] / S), 0.f);
-        s_rd[v] = nr;
-        dec += old - nr;
+        dec += v < V ? fminf(s_rd[v], C * zr[jj]) : 0.f;
       }
-      Z -= acc_sum(dec, red);
+      Z = Z0 - acc_sum(dec, red);
       R += q0v;
     }
-    if (!took) break;
+    if (took) {
+      __syncthreads();  // s_rd, s_ord and the children are read before they change
+      continue;
+    }
+    if (C > 0.f) {  // the residual that the draw takes from
+#pragma unroll
+      for (int j = 0; j < kZ; ++j) {
+        const int v = tid + j * kAccThreads;
+        if (v < V) s_rd[v] = fmaxf(s_rd[v] - C * zr[j], 0.f);
+      }
+      __syncthreads();
+    }
+    break;
   }
   // one token from the current p: mapped ids in draft-id order, then the rest;
   // chunk sums added in order (the same float expression for a chunk's end
@@ -870,14 +872,24 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
         for (int q = 0; q < W; ++q)
           if (x + q >= c1 || in_img(x + q)) a[q] = 0.f;
       });
-      const int ln = (int)group_max<64>((float)lastn);
-      if (lane == 0) s_pick = e >= 0 ? e : ln;
+      if (lane == 0) s_pick = e;
     }
   }
-  const int lo = (int)acc_max((float)lastn, red);   // its barriers publish s_pick
-  const int li = (int)acc_max((float)lasti, red);
+  __syncthreads();  // s_pick
   int pick = s_pick;
-  if (pick < 0) pick = lo >= 0 ? lo : (li >= 0 ? tgt(li) : -1);  // past the total (rounding)
+  if (pick < 0) {
+    // past the total (rounding): the owning chunk's last unmapped id with mass,
+    // else the row's, else the last mapped one
+    const float t2 = target - Mimg;
+    int ln = -1;
+    for (int x = c0 + lane; x < c1; x += 64)
+      if (!in_img(x) && p[x] > 0.f) ln = x;
+    const bool own = target >= Mimg && wn <= t2 && t2 < wn + s_cn[wave];
+    const int lown = (int)acc_max(own ? (float)ln : -1.f, red);
+    const int lo = (int)acc_max((float)ln, red);
+    const int li = (int)acc_max((float)lasti, red);
+    pick = lown >= 0 ? lown : (lo >= 0 ? lo : (li >= 0 ? tgt(li) : -1));
+  }
   if (tid <= N) {
     int32_t *acc = accepted + (size_t)b * (N + 1);
     acc[tid] = tid < len ? tok[s_path[tid + 1]] : (tid == len ? pick : -1);
@@ -911,30 +923,28 @@ hipError_t accept_sample(int B, int N, int k, int V, int Vt, const int32_t *toke
   if (k > kMaxTopk || N > kMaxLayers || V > kAccMaxV || Vt > kAccMaxVt) return hipErrorInvalidValue;
   const bool vec = Vt % 4 == 0 && ((uintptr_t)target_probs & 15u) == 0;
   float *agg = nullptr, *gathered = nullptr;
-  int32_t *agg_last = nullptr;
   if (pre.p && B <= pre.max_batch) {  // few sequences: reduce every node's row first
     const int T = 1 + N * k;
     agg = pre.p;
-    agg_last = (int32_t *)(agg + (size_t)B * T * kAccWaves * 2);
-    gathered = (float *)(agg_last + (size_t)B * T * kAccWaves);
+    gathered = agg + (size_t)B * T * kAccWaves * 2;
     const dim3 grid(B * T, kAccWaves + kAccPreGather);
     if (vec)
       hipLaunchKernelGGL(k_accept_rows<4>, grid, dim3(kAccPreThreads), 0, s, Vt, V, d2t,
-                         target_probs, img, agg, agg_last, gathered);
+                         target_probs, img, agg, gathered);
     else
       hipLaunchKernelGGL(k_accept_rows<1>, grid, dim3(kAccPreThreads), 0, s, Vt, V, d2t,
-                         target_probs, img, agg, agg_last, gathered);
+                         target_probs, img, agg, gathered);
   }
   if (vec)
     hipLaunchKernelGGL(k_accept_sample<true>, dim3(B), dim3(kAccThreads), 0, s, N, k, V, Vt,
                        tokens, retrieve, topk_draft, draft_logits, inv_temp, draft_draws, d2t,
                        target_probs, uniforms, img, accept_len, accept_path, accepted, agg,
-                       agg_last, gathered);
+                       gathered);
   else
     hipLaunchKernelGGL(k_accept_sample<false>, dim3(B), dim3(kAccThreads), 0, s, N, k, V, Vt,
                        tokens, retrieve, topk_draft, draft_logits, inv_temp, draft_draws, d2t,
                        target_probs, uniforms, img, accept_len, accept_path, accepted, agg,
-                       agg_last, gathered);
+                       gathered);
   return hipGetLastError();
 }
 
