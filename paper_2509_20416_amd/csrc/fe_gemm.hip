@@ -24,6 +24,7 @@
 //    Q/K tiles pair rotary halves (dims m and m + D/2) inside one 16-column
 //    tile; gate/up tiles pair gate row c with up row c.
 #include "fe_internal.h"
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -729,35 +730,49 @@ __global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A,
 }
 
 // Tile shapes of the many-row GEMMs and what a 64-wide K chunk of one tile
-// takes (ns, one workgroup per CU, measured at K 12288).  A launch takes the
-// shape whose rounds of workgroups cost least; K may be split over up to
-// max_slices workgroups per tile where the caller sums the slices, which costs
-// a write and a read of every slice.
-enum TileShape { kTile128x128 = 0, kTile128x192, kTile128x256, kTile256x224, kTile256x256, kTileShapes };
+// takes (ns, 32 to 64 workgroups, K 12288).  A launch takes the shape whose
+// rounds of workgroups cost least; K may be split over up to max_slices
+// workgroups per tile where the caller sums the slices, which costs a write
+// and a read of every slice.  The first shapes are for up to 256 rows only:
+// one row block holds them all, so that every weight is read once, and a
+// narrow one spreads few columns over the chip.  Measured with one workgroup
+// per CU: 147 rows x 4096 columns, K 12288 in 8 slices 28 us with 160 x 128
+// against 32 with 256 x 128; the K/V rows of seven layers (2048 columns each,
+// K 4096) 38 us with 160 x 64 against 46 with two row blocks of 128 x 128.
+enum TileShape {
+  kTile64x64 = 0, kTile96x64, kTile128x64, kTile160x64, kTile64x128, kTile96x128, kTile160x128,
+  kTile128x128, kTile128x192, kTile128x256, kTile256x224, kTile256x256, kTileShapes
+};
+constexpr int kTileFirstMany = kTile128x128;  // the shapes before serve up to 256 rows
 struct TilePick {
   int shape, ks;
 };
-constexpr int kTileM[kTileShapes] = {128, 128, 128, 256, 256};
-constexpr int kTileN[kTileShapes] = {128, 192, 256, 224, 256};
-constexpr int kTileNs[kTileShapes] = {620, 750, 830, 1180, 1240};
+constexpr int kTileM[kTileShapes] = {64, 96, 128, 160, 64, 96, 160, 128, 128, 128, 256, 256};
+constexpr int kTileN[kTileShapes] = {64, 64, 64, 64, 128, 128, 128, 128, 192, 256, 224, 256};
+constexpr int kTileNs[kTileShapes] = {320, 385, 436, 517, 480, 577, 676, 615, 750, 830, 1180, 1240};
 static TilePick pick_tile(int M, int ncols, int K, int groups, int max_slices) {
   const long nch = K / 64;
+  const double wbytes = 2.0 * groups * ncols * K;
   TilePick best{kTile128x128, 1};
   double cost = 1e30;
-  for (int t = 0; t < kTileShapes; ++t)
+  for (int t = M <= kGemmMaxRows ? 0 : kTileFirstMany; t < kTileShapes; ++t) {
+    if (t < kTileFirstMany && M > kTileM[t]) continue;
     for (int ks = 1; ks <= max_slices; ++ks) {
       if (ks > 1 && nch / ks < 8) break;  // at least 8 chunks of K per slice
       const long wgs = (long)((M + kTileM[t] - 1) / kTileM[t]) * groups * ((ncols + kTileN[t] - 1) / kTileN[t]) * ks;
       const double rounds = (double)((wgs + 255) / 256);
-      // ns; a round also fills and drains its ring and writes its tile (about
-      // 6 us); slices move at about 4 bytes per ps
-      double c = rounds * ((double)((nch + ks - 1) / ks) * kTileNs[t] + 6000.0);
+      // ns: a full chip runs at about 1 / 1.2 of the rate above, the weights
+      // stream at 4.8 TB/s at most, a round fills and drains its ring and
+      // writes its tile (about 6 us), and slices move at about 4 TB/s
+      double c = rounds * (double)((nch + ks - 1) / ks) * kTileNs[t] * 1.2;
+      c = (c > wbytes / 4800 ? c : wbytes / 4800) + rounds * 6000.0;
       if (ks > 1) c += (double)ks * M * ncols * 8 / 4000.0;
       if (c < cost) {
         cost = c;
         best = {t, ks};
       }
     }
+  }
   return best;
 }
 
@@ -765,16 +780,29 @@ static TilePick pick_tile(int M, int ncols, int K, int groups, int max_slices) {
 // groups of them, TileKv's layers), grid z over the row blocks.  128 x 128
 // tiles take a three-stage ring when the grid is about one workgroup per CU
 // (96 KB of LDS), else two stages, which lets two workgroups share a CU (1024
-// rows x 6144 columns, K 4096: 75 us with three stages, 59 with two).
-template <class Epi, bool SPLIT>
+// rows x 6144 columns, K 4096: 75 us with three stages, 59 with two).  FEW: the
+// shapes of up to 256 rows are built for this epilogue.
+template <class Epi, bool SPLIT, bool FEW>
 static hipError_t launch_tile(const TilePick &p, const bf16_t *A, int lda, int M, int K, const Epi &e,
                               int groups, float *sp, int ldp, hipStream_t s) {
   const int nb = (M + kTileM[p.shape] - 1) / kTileM[p.shape];  // row blocks per group
-  const dim3 grid((e.nvcols + kTileN[p.shape] - 1) / kTileN[p.shape], p.ks,
-                  nb * groups);
+  const dim3 grid((e.nvcols + kTileN[p.shape] - 1) / kTileN[p.shape], p.ks, nb * groups);
 #define FE_TILE(RT, NTW, WM, WN, S)                                                             \
   hipLaunchKernelGGL((k_gemm_tile<RT, NTW, WM, WN, S, Epi, SPLIT>), grid, dim3(512), 0, s, A,   \
                      lda, kDenseRows, M, K, e, sp, ldp, nb)
+  if constexpr (FEW) {
+    switch (p.shape) {
+      case kTile64x64: FE_TILE(2, 1, 2, 4, 4); break;
+      case kTile96x64: FE_TILE(3, 1, 2, 4, 4); break;
+      case kTile128x64: FE_TILE(4, 1, 2, 4, 4); break;
+      case kTile160x64: FE_TILE(5, 1, 2, 4, 4); break;
+      case kTile64x128: FE_TILE(2, 2, 2, 4, 4); break;
+      case kTile96x128: FE_TILE(3, 2, 2, 4, 4); break;
+      case kTile160x128: FE_TILE(5, 2, 2, 4, 4); break;
+      default: break;
+    }
+    if (p.shape < kTileFirstMany) return hipGetLastError();
+  }
   switch (p.shape) {
     case kTile128x128:
       if ((long)grid.x * grid.y * grid.z <= 288) FE_TILE(4, 2, 2, 4, 3);
@@ -783,7 +811,8 @@ static hipError_t launch_tile(const TilePick &p, const bf16_t *A, int lda, int M
     case kTile128x192: FE_TILE(4, 3, 2, 4, 3); break;
     case kTile128x256: FE_TILE(4, 4, 2, 4, 3); break;
     case kTile256x224: FE_TILE(4, 7, 4, 2, 2); break;
-    default: FE_TILE(8, 4, 2, 4, 2); break;
+    case kTile256x256: FE_TILE(8, 4, 2, 4, 2); break;
+    default: return hipErrorInvalidValue;
   }
 #undef FE_TILE
   return hipGetLastError();
@@ -1992,7 +2021,8 @@ constexpr int kTileNtw = 2, kTileWn = 2, kTileStages = 3, kTileRows = 64 * (4 / 
 template <class Epi>
 static hipError_t rows_unsplit(const bf16_t *A, int lda, int M, int K, const Epi &e, hipStream_t s) {
   if (K % 64 == 0)
-    return launch_tile<Epi, false>(pick_tile(M, e.nvcols, K, 1, 1), A, lda, M, K, e, 1, nullptr, 0, s);
+    return launch_tile<Epi, false, false>(pick_tile(std::max(M, kGemmMaxRows + 1), e.nvcols, K, 1, 1), A,
+                                          lda, M, K, e, 1, nullptr, 0, s);
   const dim3 grid((e.nvcols + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
   hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, Epi>), grid, dim3(256), 0, s,
                      A, lda, kDenseRows, M, K, e, nullptr, 0);
@@ -2015,11 +2045,11 @@ hipError_t gemm_store_rows(const void *A, int lda, int M, int K, const void *W, 
                                                         ldo, (const bf16_t *)embed, tokens, vocab,
                                                         (bf16_t *)gather_out, ld_gather, d, M};
   e.lda = lda;
-  if (K % 64 == 0 && ncols % 8 == 0) {
+  if (K % 64 == 0 && ncols % 8 == 0 && ss && ss->p) {
     const TilePick p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
-    if (p.ks > 1) {
+    if (p.ks > 1 || M <= kGemmMaxRows) {
       const int ldp = (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape];
-      const hipError_t err = launch_tile<EpiStore<bf16_t>, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
+      const hipError_t err = launch_tile<EpiStore<bf16_t>, true, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
                                                                  ss->p, ldp, s);
       if (err != hipSuccess) return err;
       hipLaunchKernelGGL(k_store_rows, dim3(M), dim3(256), 0, s, (const float *)ss->p, ldp, p.ks, M,
@@ -2049,10 +2079,10 @@ hipError_t gemm_resid_rows(const void *A, int lda, int M, int K, const void *W, 
   SplitOut so;
   TilePick p{kTile128x128, 1};
   if (K % 64 == 0) p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
-  if (p.ks > 1) {
+  if (p.ks > 1 || (K % 64 == 0 && M <= kGemmMaxRows && ss && ss->p)) {
     const EpiResid<bf16_t> e{(const bf16_t *)W, K, ncols, out, ldo, resid, ldr, nullptr, 1, 0, GainCopies{}};
     so = SplitOut{ss->p, (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape], p.ks};
-    const hipError_t err = launch_tile<EpiResid<bf16_t>, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
+    const hipError_t err = launch_tile<EpiResid<bf16_t>, true, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
                                                                ss->p, so.ldp, s);
     if (err != hipSuccess) return err;
   } else {
@@ -2098,21 +2128,12 @@ hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int 
                        (const bf16_t *)A, lda, kDenseRows, M, layers[0].d, *na, e);
     return hipGetLastError();
   }
-  e.g.nblocks = (M + kTileRows - 1) / kTileRows;
-  if (M < kTileRows) {
-    // one row block: the weights are the work, so narrower column tiles give
-    // every compute unit a share of them
-    constexpr int cols = 16 * 1 * kTileWn;
-    const dim3 grid((e.nvcols + cols - 1) / cols, 1, e.g.nblocks * nlayers);
-    hipLaunchKernelGGL((k_gemm_mid<bf16_t, 1, kTileWn, kTileStages, TileKv>), grid, dim3(256), 0, s,
-                       (const bf16_t *)A, lda, kDenseRows, M, layers[0].d, e, nullptr, 0);
-    return hipGetLastError();
-  }
   if (layers[0].d % 64 == 0) {
     const TilePick p = pick_tile(M, e.nvcols, layers[0].d, nlayers, 1);
     e.g.nblocks = (M + kTileM[p.shape] - 1) / kTileM[p.shape];
-    return launch_tile<TileKv, false>(p, (const bf16_t *)A, lda, M, layers[0].d, e, nlayers, nullptr, 0, s);
+    return launch_tile<TileKv, false, true>(p, (const bf16_t *)A, lda, M, layers[0].d, e, nlayers, nullptr, 0, s);
   }
+  e.g.nblocks = (M + kTileRows - 1) / kTileRows;
   const dim3 grid((e.nvcols + kTileCols - 1) / kTileCols, 1, e.g.nblocks * nlayers);
   hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, TileKv>), grid, dim3(256), 0,
                      s, (const bf16_t *)A, lda, kDenseRows, M, layers[0].d, e, nullptr, 0);

@@ -388,7 +388,7 @@ hipError_t gemm_swiglu_rows(const void *A, int lda, int M, int K, const void *w_
 // Every layer's K/V projection into its cache in one launch (bf16): layer l's
 // normalised rows at A + l * a_layer_stride.  With na (M <= 16) A holds
 // gamma * x per layer and the rows' 1/rms come from na's sums of squares;
-// otherwise tiles of 128 or 256 rows (32 columns wide below 128 rows).
+// otherwise 2-D tiles.
 hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int nlayers,
                         const KvCacheArgs *layers, const NormA *na, hipStream_t s);
 

@@ -1322,8 +1322,9 @@ fe_status kv_update_impl(fe_drafter *h, int32_t n_rows, const void *features,
       FE_TRY(gemm_kv_rows(an, d, (long)C * d, Mc, c.n_layers, la, &na, s));
       continue;
     }
-    if (dt && Mc >= kTiledRows) {
-      // many rows: one launch per stage over 2-D tiles
+    const bool rows = dt && (Mc >= kTiledRows || (!self && d % 64 == 0));
+    if (rows) {
+      // one launch per stage over 2-D tiles, and a pass over the rows after each FC
       // (matrix-core bound from a few hundred rows)
       FE_TRY(gemm_store_rows((const char *)features + (size_t)r0 * F * d * es, F * d, Mc, F * d,
                              h->w.w_fuse, d, cat, 2 * d, h->w.embed, tokens + r0, c.target_vocab,
@@ -1360,7 +1361,7 @@ fe_status kv_update_impl(fe_drafter *h, int32_t n_rows, const void *features,
     }
     if (dt) {
       // every layer's normalised rows from one RMS per row (one launch)
-      if (Mc < kTiledRows) {
+      if (!rows) {
         RmsCopies rc{};
         rc.n = c.n_layers;
         for (int l = 0; l < c.n_layers; ++l) {

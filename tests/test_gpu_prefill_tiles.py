@@ -100,3 +100,14 @@ def test_cascade_rows_over_tiles_match_oracle(layers):
     cfg = C.SMALL_MHA_BF16_D128.with_(n_q_heads=16, n_kv_heads=16, n_layers=layers, name="wide_kv")
     up = make_update_rows(cfg, np.array([400, 77]), np.array([0, 5]), capacity=400, seed=14)
     _run(cfg, up, 1024)
+
+
+# 17 to 256 rows: one row block of 64, 96, 128 or 160 rows, 64 columns wide for
+# two layers' K/V and 128 wide for seven; above 160 rows two blocks
+@pytest.mark.parametrize("rows", [17, 64, 65, 96, 128, 129, 160, 161, 256])
+@pytest.mark.parametrize("layers", [2, 7])
+def test_few_rows_over_tiles_match_oracle(layers, rows):
+    from tests.test_gpu_kv_update import _run
+    cfg = C.SMALL_MHA_BF16_D128.with_(n_q_heads=16, n_kv_heads=16, n_layers=layers, name="wide_kv")
+    up = make_update_rows(cfg, np.array([rows - 5, 5]), np.array([0, 40]), capacity=256, seed=rows)
+    _run(cfg, up, 1024)
