@@ -31,7 +31,6 @@
 namespace fe {
 
 template <typename T> __device__ __forceinline__ void mma16(f32x4 &acc, u32x4 a, u32x4 b);
-template <typename T> struct EpiLm;
 
 template <> __device__ __forceinline__ void mma16<uint16_t>(f32x4 &acc, u32x4 a, u32x4 b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -577,13 +576,11 @@ __global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A,
   // The epilogue takes FP of the NTW column tiles per pass.  Its tile rows are
   // 4 floats longer than the span: 16-byte aligned for the vector reads, and
   // the accumulator writes (4 rows x 16 columns per instruction) land on
-  // distinct banks; one float longer for the LM head's scan (a thread per row:
-  // consecutive rows on distinct banks)
-  constexpr bool kLm = std::is_same<Epi, EpiLm<bf16_t>>::value;
+  // distinct banks
   constexpr int kMaxTile = 140 * 1024;
   constexpr int FP = BM * (BN + 4) * 4 <= kMaxTile ? NTW : (NTW + 1) / 2;
-  constexpr int PN = 16 * FP * WN, LDT = PN + (kLm ? 1 : 4), TILE = BM * LDT * 4;
-  static_assert(TILE <= kMaxTile && PN % 32 == 0 && (!kLm || FP == NTW), "epilogue passes");
+  constexpr int PN = 16 * FP * WN, LDT = PN + 4, TILE = BM * LDT * 4;
+  static_assert(TILE <= kMaxTile && PN % 32 == 0, "epilogue passes");
   constexpr int SMEM = SPLIT || S * STAGE > TILE ? S * STAGE : TILE;
   static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
@@ -1551,8 +1548,26 @@ struct TileSwiglu : EpiSwiglu<bf16_t> {
   }
 };
 
-// Shared LM head: per (row, column tile) max, sum of exp(z - max) and the top-k
-// (largest logit first, equal logits by lower draft id); logits optionally kept.
+// Maximum / minimum over 16 lanes (one DPP row), in every lane of the row.
+__device__ __forceinline__ uint32_t row16_max(uint32_t x) {
+  auto d = [](uint32_t v, auto ctrl) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  x = max(x, d(x, std::integral_constant<int, 0xB1>{}));
+  x = max(x, d(x, std::integral_constant<int, 0x4E>{}));
+  x = max(x, d(x, std::integral_constant<int, 0x141>{}));
+  return max(x, d(x, std::integral_constant<int, 0x128>{}));
+}
+
+// Shared LM head: per (row, 64-column tile) max, sum of exp(z - max) and the
+// top-k (largest key first, equal keys by lower draft id); logits optionally
+// kept.  Sixteen lanes take a (row, tile), four adjacent columns each, so a wave
+// does four at a time, whatever the row count: the logits leave as whole
+// vectors, a generator block's four draws are a lane's four columns, and a
+// selection round is one DPP maximum of 32-bit keys.  (A thread per row, as
+// rows above 16 had it, left most of a workgroup idle while 64 or 128 columns
+// went by one after the other: the 30-row LM head of 32000 x 4096 took 93 us,
+// the 224-row one 111.)
 template <typename T> struct EpiLm {
   static constexpr bool kRowStream = false, kSplitK = false;
   using Pre = NoPre;
@@ -1562,161 +1577,126 @@ template <typename T> struct EpiLm {
   int ldw, nvcols;
   __device__ const T *wrow(int c) const { return (const T *)a.w + (size_t)c * ldw; }
 
-  // Many rows (batched drafting): thread = row.  The tile's columns are
-  // scanned in increasing id order into a sorted list of KL (value, id)
-  // pairs; an equal value never displaces an earlier entry, so ties go to the
-  // lower id without comparing ids.  NaN compares false and is never taken.
-  // selection key of tempered logit xt at column col of row m: xt, or
-  // xt + Gumbel(u) = xt - log(-log(u)) for sampling without replacement
-  __device__ float sel_key(float xt, int m, int col) const {
-    if (!a.draws.on()) return xt;
-    const float u = a.draws.at((uint64_t)m * nvcols + col);
-    return xt - logf(-logf(u));
-  }
-
-  template <int KL>
-  __device__ void finish_rows(const float *tile, int ldt, int M, int c0, int span) const {
-    const int m = threadIdx.x;
-    if (m >= M) return;
-    const int nvalid = min(span, nvcols - c0);
-    const int nwg = gridDim.x, tileid = blockIdx.x;
-    const float *row = tile + m * ldt;
-    float mx = -INFINITY;
-    for (int c = 0; c < nvalid; ++c) mx = fmaxf(mx, row[c] * a.inv_temp);
-    float se = 0.f;
-    float vs[KL], zs[KL];
-    int is[KL];
-#pragma unroll
-    for (int j = 0; j < KL; ++j) {
-      vs[j] = -INFINITY;
-      zs[j] = -INFINITY;
-      is[j] = 0x7fffffff;
-    }
-    // counter-based draws: one generator block per four consecutive columns
-    const bool gen = a.draws.so != nullptr;
-    const uint64_t seed = gen ? a.draws.so[0] : 0, offset = gen ? a.draws.so[1] : 0;
-    uint64_t have = ~0ull;
-    float ub[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nvalid; ++c) {
-      const float x = row[c], xt = x * a.inv_temp;
-      float key = xt;
-      if (gen) {
-        const uint64_t e = (uint64_t)m * nvcols + c0 + c;
-        if ((e >> 2) != have) {
-          have = e >> 2;
-          philox_block(seed, offset, have, ub);
-        }
-        const int w = (int)(e & 3);
-        const float u = w == 0 ? ub[0] : w == 1 ? ub[1] : w == 2 ? ub[2] : ub[3];
-        key = xt - logf(-logf(u));
-      } else {
-        key = sel_key(xt, m, c0 + c);
-      }
-      se += expf(xt - mx);
-      if (a.logits) a.logits[(size_t)m * nvcols + c0 + c] = x;
-      if (!(vs[KL - 1] < key)) continue;  // not in the list: nothing below would change
-#pragma unroll
-      for (int j = KL - 1; j >= 1; --j) {
-        const bool prev = vs[j - 1] < key, here = vs[j] < key;
-        vs[j] = prev ? vs[j - 1] : (here ? key : vs[j]);
-        zs[j] = prev ? zs[j - 1] : (here ? xt : zs[j]);
-        is[j] = prev ? is[j - 1] : (here ? c0 + c : is[j]);
-      }
-      if (vs[0] < key) {
-        vs[0] = key;
-        zs[0] = xt;
-        is[0] = c0 + c;
-      }
-    }
-    const size_t pb = (size_t)m * nwg + tileid;
-    a.part_max[pb] = mx;
-    a.part_sum[pb] = se;
-#pragma unroll
-    for (int j = 0; j < KL; ++j)
-      if (j < a.topk) {
-        a.cand_val[pb * kMaxTopk + j] = is[j] != 0x7fffffff ? vs[j] : -INFINITY;
-        a.cand_idx[pb * kMaxTopk + j] = is[j];
-        if (a.draws.on()) a.cand_z[pb * kMaxTopk + j] = zs[j];
-      }
-  }
-
+  // Selection key of tempered logit x: x, or with draws x + Gumbel(u) = x -
+  // log(-log(u)) (sampling without replacement).  Ordered as 32-bit integers:
+  // 0 is no candidate, 1 a NaN (listed after every number for up to 16 rows,
+  // else no candidate), the rest the order-preserving bits of the float.
   __device__ void finish(float *tile, int ldt, int M, int c0, int span, const Pre &) const {
-    if (M > 16) {
-      if (a.topk <= 2) finish_rows<2>(tile, ldt, M, c0, span);
-      else if (a.topk <= 4) finish_rows<4>(tile, ldt, M, c0, span);
-      else if (a.topk <= 8) finish_rows<8>(tile, ldt, M, c0, span);
-      else finish_rows<16>(tile, ldt, M, c0, span);
-      return;
-    }
+    // with more items than one round of the waves, two at a time: a round's
+    // maxima are a chain, and the other item's fill its gaps
+    if (M * (span >> 6) > (int)(blockDim.x >> 4)) finish_items<2>(tile, ldt, M, c0, span);
+    else finish_items<1>(tile, ldt, M, c0, span);
+  }
+  template <int U>
+  __device__ void finish_items(const float *tile, int ldt, int M, int c0, int span) const {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int nvalid = min(span, nvcols - c0);
-    const int nwg = gridDim.x, tileid = blockIdx.x;
-    for (int m = wave; m < M; m += nw) {
-      const float *row = tile + m * ldt;
-      constexpr int PER = 4;  // span <= 256
-      float v[PER];
-      int id[PER];
-      float mx = -INFINITY;
+    const int l16 = lane & 15, base = lane & 48;
+    const int nseg = span >> 6, items = M * nseg, ntile = (nvcols + 63) >> 6;
+    const bool vec = aligned16(a.logits), gen = a.draws.so != nullptr, on = a.draws.on();
+    const uint32_t nan_key = M <= 16 ? 1u : 0u;
+    const uint64_t seed = gen ? a.draws.so[0] : 0, offset = gen ? a.draws.so[1] : 0;
+    for (int i0 = 4 * U * wave; i0 < items; i0 += 4 * U * nw) {
+      float v[U][4], mx[U], se[U];
+      uint32_t key[U][4];
+      bool live[U];
+      size_t pb[U];
+      int cs[U];
 #pragma unroll
-      for (int p = 0; p < PER; ++p) {
-        const int c = lane + 64 * p;
-        const bool ok = c < nvalid;
-        v[p] = ok ? row[c] : -INFINITY;
-        id[p] = ok ? c0 + c : 0x7fffffff;
-        if (a.logits && ok) a.logits[(size_t)m * nvcols + id[p]] = v[p];
-        v[p] *= a.inv_temp;   // statistics and candidates at temperature T
-        mx = fmaxf(mx, v[p]);
-      }
-      mx = group_max<64>(mx);
-      float se = 0.f;
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + 4 * u + (lane >> 4), it = min(i, items - 1), m = it / nseg, seg = it % nseg;
+        cs[u] = c0 + 64 * seg;                                 // the tile's first column
+        live[u] = i < items && cs[u] < nvcols;
+        const bool ok = live[u] && cs[u] + 4 * l16 < nvcols;   // the vocabulary is a multiple of 16
+        pb[u] = (size_t)m * ntile + (cs[u] >> 6);
+        const float *t = tile + m * ldt + 64 * seg + 4 * l16;
+        const size_t e0 = (size_t)m * nvcols + cs[u] + 4 * l16;
+        if ((ldt & 3) == 0) {
+          const f32x4 x = *reinterpret_cast<const f32x4 *>(t);
+          v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
+        } else {
 #pragma unroll
-      for (int p = 0; p < PER; ++p) se += (id[p] != 0x7fffffff) ? expf(v[p] - mx) : 0.f;
-      se = group_sum<64>(se);
-      const size_t pb = (size_t)m * nwg + tileid;
-      if (lane == 0) {
-        a.part_max[pb] = mx;
-        a.part_sum[pb] = se;
-      }
-      uint64_t key[PER];
-      const uint64_t e0 = (uint64_t)m * nvcols + c0;  // uniform of column c0
-      if (a.draws.so != nullptr && (e0 & 3) == 0) {
-        // counter-based draws, block-aligned tile row: lane q draws block
-        // e0/4 + q (columns 4q .. 4q+3), and lane l takes column l + 64p's
-        // uniform from lane l/4 + 16p, word l & 3
-        float ub[4];
-        philox_block(a.draws.so[0], a.draws.so[1], (e0 >> 2) + lane, ub);
-        const int w = lane & 3;
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-          const int src = (lane >> 2) + 16 * p;
-          const float u0 = __shfl(ub[0], src, 64), u1 = __shfl(ub[1], src, 64);
-          const float u2 = __shfl(ub[2], src, 64), u3 = __shfl(ub[3], src, 64);
-          const float u = w == 0 ? u0 : w == 1 ? u1 : w == 2 ? u2 : u3;
-          key[p] = id[p] != 0x7fffffff ? topk_key(v[p] - logf(-logf(u)), id[p]) : kNoKey;
+          for (int q = 0; q < 4; ++q) v[u][q] = t[q];
         }
-      } else {
+        if (a.logits && ok) {
+          if (vec) {
+            *reinterpret_cast<f32x4 *>(a.logits + e0) = f32x4{v[u][0], v[u][1], v[u][2], v[u][3]};
+          } else {
 #pragma unroll
-        for (int p = 0; p < PER; ++p)
-          key[p] = id[p] != 0x7fffffff ? topk_key(sel_key(v[p], m, id[p]), id[p]) : kNoKey;
+            for (int q = 0; q < 4; ++q) a.logits[e0 + q] = v[u][q];
+          }
+        }
+        mx[u] = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v[u][q] = ok ? v[u][q] * a.inv_temp : -INFINITY;  // statistics and candidates at temperature T
+          mx[u] = fmaxf(mx[u], v[u][q]);
+        }
+        mx[u] = group_max<16>(mx[u]);
+        se[u] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) se[u] += ok ? expf(v[u][q] - mx[u]) : 0.f;
+        se[u] = group_sum<16>(se[u]);
+        float n[4];
+        if (gen) {
+          philox_block(seed, offset, (uint64_t)e0 >> 2, n);  // columns 4 l16 .. + 3 of the row
+        } else if (on) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) n[q] = ok ? a.draws.u[e0 + q] : 0.5f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float kf = on ? v[u][q] - logf(-logf(n[q])) : v[u][q];
+          const uint32_t w = __float_as_uint(kf);
+          key[u][q] = !ok ? 0u : kf != kf ? nan_key : (w & 0x80000000u) ? ~w : (w | 0x80000000u);
+        }
+      }
+      uint32_t got[U];  // lane r: the r-th best key, its column and its z / T
+      int gcol[U];
+      float gz[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        got[u] = 0;
+        gcol[u] = 0;
+        gz[u] = -INFINITY;
       }
       for (int r = 0; r < a.topk; ++r) {
-        // lane-local best, then wave max of the ordering keys (lower id wins ties)
-        uint64_t best = kNoKey;
 #pragma unroll
-        for (int p = 0; p < PER; ++p) best = key[p] > best ? key[p] : best;
-        best = wave_max_u64(best);
-        float zb = -INFINITY;  // z / T of the winner, from the lane that holds it
+        for (int u = 0; u < U; ++u) {
+          uint32_t(&k)[4] = key[u];
+          const uint32_t best = row16_max(max(max(k[0], k[1]), max(k[2], k[3])));
+          // the lowest column that holds it (as 64 - column, so a maximum finds it)
+          uint32_t inv = 0;
 #pragma unroll
-        for (int p = 0; p < PER; ++p) {
-          zb = key[p] == best ? v[p] : zb;
-          key[p] = key[p] == best ? kNoKey : key[p];
+          for (int q = 3; q >= 0; --q) inv = k[q] == best ? 64u - 4 * l16 - q : inv;
+          const int col = 64 - (int)row16_max(inv);
+          if (on) {
+            const int q = col & 3;
+            const float z = __shfl(q == 0 ? v[u][0] : q == 1 ? v[u][1] : q == 2 ? v[u][2] : v[u][3],
+                                   base + (col >> 2), 64);
+            if (l16 == r) gz[u] = z;
+          }
+          if (l16 == r) {
+            got[u] = best;
+            gcol[u] = col;
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) k[q] = col == 4 * l16 + q ? 0u : k[q];
         }
-        if (a.draws.on()) zb = group_max<64>(zb);
-        if (lane == 0) {
-          const bool got = best != kNoKey;
-          a.cand_val[pb * kMaxTopk + r] = got ? topk_key_value(best) : -INFINITY;
-          a.cand_idx[pb * kMaxTopk + r] = got ? topk_key_id(best) : 0x7fffffff;
-          if (a.draws.on()) a.cand_z[pb * kMaxTopk + r] = got ? zb : -INFINITY;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (!live[u]) continue;
+        if (l16 == 0) {
+          a.part_max[pb[u]] = mx[u];
+          a.part_sum[pb[u]] = se[u];
+        }
+        if (l16 < a.topk) {
+          const uint32_t g = got[u];
+          const float val = g == 1u ? __int_as_float(0x7fc00000)
+                                    : __uint_as_float((g & 0x80000000u) ? (g & 0x7fffffffu) : ~g);
+          a.cand_val[pb[u] * kMaxTopk + l16] = g ? val : -INFINITY;
+          a.cand_idx[pb[u] * kMaxTopk + l16] = g ? cs[u] + gcol[u] : 0x7fffffff;
+          if (on) a.cand_z[pb[u] * kMaxTopk + l16] = g ? gz[u] : -INFINITY;
         }
       }
     }
@@ -2163,11 +2143,10 @@ hipError_t gemm_lmhead(int dt, const void *A, int lda, const ARows &arows, int M
   *nwg_out = lmhead_tiles(a.V);
   if (dt && !na && M > 128 && M <= 256 && K % 64 == 0) {
     // many rows (batched drafting, B x N of them): every row in one 256 x 128
-    // tile of k_gemm_tile, so the head is streamed once; 128-column tiles
-    // (half as many as lmhead_tiles counts)
+    // tile of k_gemm_tile, so the head is streamed once (two of lmhead_tiles'
+    // tiles per workgroup)
     EpiLm<bf16_t> e{a, K, a.V};
     const int gx = (a.V + 127) / 128;
-    *nwg_out = gx;
     hipLaunchKernelGGL((k_gemm_tile<4, 4, 4, 2, 3, EpiLm<bf16_t>>), dim3(gx), dim3(512), 0, s,
                        (const bf16_t *)A, lda, arows, M, K, e, nullptr, 0, 1);
     return hipGetLastError();
