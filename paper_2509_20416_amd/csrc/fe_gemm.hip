@@ -240,13 +240,13 @@ __global__ __launch_bounds__(64 * WK * WN) void k_gemm(const T *__restrict__ A, 
 }
 
 // ---------------------------------------------------------------------------
-// Row-streaming path for 1..8 input rows (batch-1 layers, bf16 weights): no
-// matrix cores, no weight staging.  A workgroup of W waves owns SPAN = 4W
+// Row-streaming path for 1..4 input rows (batch-1 layers): no matrix cores, no
+// weight staging.  A workgroup of W waves owns SPAN = 4W
 // virtual columns; wave w takes weight rows 4w..4w+3 with 16 lanes per row,
 // so every load instruction reads 256 contiguous bytes of each of 4 rows and
-// a lane only ever accumulates its own row.  The input rows are in LDS as
-// bf16 (zero-padded to a multiple of 128) and meet the weights in
-// v_dot2c_f32_bf16 as they arrive; two register banks of kGvDepth pieces per
+// a lane only ever accumulates its own row.  The input rows are in LDS in the
+// storage type (zero-padded to whole pieces) and meet the weights in
+// v_dot2c_f32_bf16, or in fp32 multiply-adds, as they arrive; two register banks of kGvDepth pieces per
 // lane alternate, one in flight while the other is consumed.  Each row's sum
 // is reduced over its 16 lanes with DPP; the [M, SPAN] tile goes to the same
 // epilogues as the matrix-core paths.
@@ -266,9 +266,21 @@ __device__ __forceinline__ float dot8(u32x4 w, u32x4 x, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w3), __builtin_bit_cast(bf16x2_t, x3), acc, false);
 }
 
-template <int MR, int W, bool NORM, class Epi>
-__global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, int lda, ARows arows,
+// One 16-byte piece of a weight row times the same piece of an input row.
+__device__ __forceinline__ float dot_piece(bf16_t, u32x4 w, u32x4 x, float acc) { return dot8(w, x, acc); }
+__device__ __forceinline__ float dot_piece(float, u32x4 w, u32x4 x, float acc) {
+  const f32x4 a = __builtin_bit_cast(f32x4, w), b = __builtin_bit_cast(f32x4, x);
+  acc = fmaf(a.x, b.x, acc);
+  acc = fmaf(a.y, b.y, acc);
+  acc = fmaf(a.z, b.z, acc);
+  return fmaf(a.w, b.w, acc);
+}
+
+template <typename T, int MR, int W, bool NORM, class Epi>
+__global__ __launch_bounds__(64 * W) void k_gemv(const T *__restrict__ A, int lda, ARows arows,
                                                  int M, int K, NormA na, Epi epi) {
+  constexpr int E = Elt<T>::kPer16B;  // elements per 16-byte piece
+  constexpr int PE = 16 * E;          // a row's elements per load instruction
   constexpr int SPAN = 4 * W;
   constexpr int NTHR = 64 * W;
   extern __shared__ __attribute__((aligned(16))) char xs_raw[];
@@ -276,17 +288,17 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, i
   __shared__ float s_inv[MR];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rq = lane >> 4, l16 = lane & 15;
   const int c0 = blockIdx.x * SPAN;
-  const int kpad = (K + 127) & ~127;
-  const int npc = kpad / 128;  // 16-byte pieces per lane per row
-  bf16_t *xs = reinterpret_cast<bf16_t *>(xs_raw);
+  const int kpad = (K + PE - 1) / PE * PE;
+  const int npc = kpad / PE;  // 16-byte pieces per lane per row
+  T *xs = reinterpret_cast<T *>(xs_raw);
 
   // weight row of this lane (clamped; columns past the end are dropped at the end)
   const int col = c0 + wave * 4 + rq;
-  const bf16_t *wr = epi.wrow(min(col, epi.nvcols - 1));
-  // piece p of the row: elements p*128 + 8*l16 .. +7; past K the address is
+  const T *wr = epi.wrow(min(col, epi.nvcols - 1));
+  // piece p of the row: elements p*PE + E*l16 ..; past K the address is
   // clamped in bounds and the (finite) weights meet zero-padded inputs
   auto ldw = [&](int p) {
-    return ldg_stream(reinterpret_cast<const u32x4 *>(wr + min(p * 128 + l16 * 8, K - 8)));
+    return ldg_stream(reinterpret_cast<const u32x4 *>(wr + min(p * PE + l16 * E, K - E)));
   };
   // every independent load is issued before anything is consumed, so the
   // whole prologue costs one memory round trip: the first weight pieces, the
@@ -296,13 +308,13 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, i
   for (int i = 0; i < kGvDepth; ++i) ba[i] = ldw(min(i, npc - 1));
 
   constexpr int XPT = kGvMaxLds / 16 / NTHR;  // input pieces per thread, at most
-  const int xper = kpad / 8, xtot = MR * xper;
+  const int xper = kpad / E, xtot = MR * xper;
   u32x4 xr[XPT];
 #pragma unroll
   for (int u = 0; u < XPT; ++u)
     if (NTHR * u < xtot) {  // uniform: batch u holds at least one piece
       const int idx = min(tid + NTHR * u, xtot - 1);
-      const int m = idx / xper, e = min((idx % xper) * 8, K - 8);
+      const int m = idx / xper, e = min((idx % xper) * E, K - E);
       xr[u] = *reinterpret_cast<const u32x4 *>(A + (size_t)arows.row(min(m, M - 1)) * lda + e);
     }
 
@@ -323,7 +335,7 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, i
   for (int u = 0; u < XPT; ++u) {
     const int idx = tid + NTHR * u;
     if (NTHR * u < xtot && idx < xtot) {
-      const int m = idx / xper, e = (idx % xper) * 8;
+      const int m = idx / xper, e = (idx % xper) * E;
       *reinterpret_cast<u32x4 *>(xs + (size_t)m * kpad + e) = (m < M && e < K) ? xr[u] : zero;
     }
   }
@@ -342,7 +354,7 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, i
   float acc[MR];
 #pragma unroll
   for (int m = 0; m < MR; ++m) acc[m] = 0.f;
-  const bf16_t *xl = xs + l16 * 8;
+  const T *xl = xs + l16 * E;
   auto consume = [&](const u32x4 (&bw)[kGvDepth], int p0) {
 #pragma unroll
     for (int i = 0; i < kGvDepth; ++i) {
@@ -350,7 +362,7 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const bf16_t *__restrict__ A, i
       if (p < npc) {
 #pragma unroll
         for (int m = 0; m < MR; ++m)
-          acc[m] = dot8(bw[i], *reinterpret_cast<const u32x4 *>(xl + (size_t)m * kpad + p * 128), acc[m]);
+          acc[m] = dot_piece(T(), bw[i], *reinterpret_cast<const u32x4 *>(xl + (size_t)m * kpad + p * PE), acc[m]);
       }
     }
   };
@@ -1712,15 +1724,15 @@ template <int WKmax, int MT> struct SplitK {
   static constexpr int value = WKmax < cap ? WKmax : cap;
 };
 
-template <class Epi>
-static hipError_t run_gemv(const bf16_t *A, int lda, const ARows &arows, int M, int K,
+template <typename T, class Epi>
+static hipError_t run_gemv(const T *A, int lda, const ARows &arows, int M, int K,
                            const Epi &epi, const NormA *na, int mr, size_t lds, hipStream_t s) {
   constexpr int W = 4 * (Epi::kMidNtwMin > 1 ? Epi::kMidNtwMin : 1);  // SPAN = 16 * kMidNtwMin
   constexpr int SPAN = 4 * W;
   const int grid = (epi.nvcols + SPAN - 1) / SPAN;
   const NormA n0 = na ? *na : NormA{nullptr, 0, 1, 0, 1, 1, 0.f};
 #define FE_GEMV(MRV, NORMV)                                                                      \
-  hipLaunchKernelGGL((k_gemv<MRV, W, NORMV, Epi>), dim3(grid), dim3(64 * W), lds, s, A, lda, arows, \
+  hipLaunchKernelGGL((k_gemv<T, MRV, W, NORMV, Epi>), dim3(grid), dim3(64 * W), lds, s, A, lda, arows, \
                      M, K, n0, epi)
 #define FE_GEMV_M(NORMV)              \
   switch (mr) {                       \
@@ -1765,14 +1777,17 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
   const int grid = (epi.nvcols + SPAN - 1) / SPAN;
   const int mt = (M + 15) / 16;
   const NormA n0 = na ? *na : NormA{nullptr, 0, 1, 0, 1, 1, 0.f};
-  if constexpr (sizeof(T) == 2) {
-    // up to 4 rows whose padded input rows fit the LDS budget: row streaming
-    // (the LM head's per-row top-k is cheaper on the matrix-core tiles)
-    if constexpr (Epi::kRowStream) {
-      const int mr = M <= 1 ? 1 : M <= 2 ? 2 : 4;
-      const size_t lds = (size_t)mr * ((K + 127) & ~127) * 2;
-      if (M <= 4 && lds <= (size_t)kGvMaxLds && K >= 8) return run_gemv(A, lda, arows, M, K, epi, na, mr, lds, s);
-    }
+  // up to 4 rows whose padded input rows fit the LDS budget: row streaming
+  // (the LM head's per-row top-k is cheaper on the matrix-core tiles).  fp32
+  // rows took the matrix-core tiles before: their launches are all latency,
+  // and those load the epilogue's values only after the products (the tiny
+  // drafter's 256- to 768-wide rows: 6.2 us a launch, 4.6 so).
+  if constexpr (Epi::kRowStream) {
+    constexpr int PE = 16 * Elt<T>::kPer16B;
+    const int mr = M <= 1 ? 1 : M <= 2 ? 2 : 4;
+    const size_t lds = (size_t)mr * ((K + PE - 1) / PE * PE) * sizeof(T);
+    if (M <= 4 && lds <= (size_t)kGvMaxLds && K >= Elt<T>::kPer16B)
+      return run_gemv<T>(A, lda, arows, M, K, epi, na, mr, lds, s);
   }
   if (na) {
     if (mt != 1) return hipErrorInvalidValue;
