@@ -1802,7 +1802,17 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
   bool splittable = false;
   if constexpr (Epi::kSplitK) splittable = ss != nullptr && ss->p != nullptr;
   const bool ring_wide = mt == 2 && (epi.nvcols >= 64 * 256 || splittable);
-  if (mt <= 2 && !ring_wide) {
+  // 5..16 rows: k_gemm's 16-column workgroups are few, and when they don't fill
+  // whole rounds of CUs, those with one more set the time (5120 columns: 320
+  // workgroups on 256 CUs, 12 rows: 2.8 TB/s against 4.3 for 4096 columns).
+  // Split-K slices spread the columns evenly for a finish launch of about 6 us,
+  // which the lost share of the stream (at 4.3 TB/s) has to exceed.
+  bool uneven = false;
+  if (sizeof(T) == 2 && mt == 1 && splittable) {
+    const double fill = (double)grid / ((grid + 255) / 256 * 256);
+    uneven = 2.0 * epi.nvcols * K / 4.3e6 * (1.0 / fill - 1.0) > 6.0;
+  }
+  if (mt <= 2 && !ring_wide && !uneven) {
     if (mt <= 1)
       hipLaunchKernelGGL((k_gemm<T, 1, NT, SplitK<WKmax, 1>::value, WN, false, Epi>), dim3(grid),
                          dim3(64 * SplitK<WKmax, 1>::value * WN), 0, s, A, lda, arows, M, K, n0, epi);
@@ -1870,7 +1880,7 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
     const int gx = (epi.nvcols + 127) / 128, nchk = (K + KC - 1) / KC;
     // about one workgroup per CU (k_splitk_finish sums at most 8 slices); many
     // rows make each slice heavier and its partial sums larger: fewer slices
-    ks = min(M > 128 ? 4 : kSliceCap32, max(1, (kSliceWgs + gx - 1) / gx));
+    ks = min(M > 128 ? 4 : kSliceCap32, max(1, kSliceWgs / gx));
     ks = min(ks, kMaxSlices);
     ks = min(ks, max(1, nchk / 4));  // a few chunks per slice for the ring
     ldp = gx * 128;
