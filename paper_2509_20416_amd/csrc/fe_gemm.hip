@@ -738,16 +738,20 @@ __global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A,
   }
 }
 
+// split-K slices the reductions sum (k_splitk_finish, k_resid_rows)
+constexpr int kMaxSlices = 8;
+
 // Tile shapes of the many-row GEMMs and what a 64-wide K chunk of one tile
 // takes (ns, 32 to 64 workgroups, K 12288).  A launch takes the shape whose
-// rounds of workgroups cost least; K may be split over up to max_slices
-// workgroups per tile where the caller sums the slices, which costs a write
-// and a read of every slice.  The first shapes are for up to 256 rows only:
-// one row block holds them all, so that every weight is read once, and a
-// narrow one spreads few columns over the chip.  Measured with one workgroup
-// per CU: 147 rows x 4096 columns, K 12288 in 8 slices 28 us with 160 x 128
-// against 32 with 256 x 128; the K/V rows of seven layers (2048 columns each,
-// K 4096) 38 us with 160 x 64 against 46 with two row blocks of 128 x 128.
+// rounds of workgroups cost least; K may be split over as many workgroups per
+// tile (at most kMaxSlices) as slices of its padded columns fit in `floats`,
+// where the caller sums the slices, which costs a write and a read of each.
+// The first shapes are for up to 256 rows only: one row block holds them all,
+// so that every weight is read once, and a narrow one spreads few columns over
+// the chip.  Measured with one workgroup per CU: 147 rows x 4096 columns,
+// K 12288 in 8 slices 28 us with 160 x 128 against 32 with 256 x 128; the K/V
+// rows of seven layers (2048 columns each, K 4096) 38 us with 160 x 64 against
+// 46 with two row blocks of 128 x 128.
 enum TileShape {
   kTile64x64 = 0, kTile96x64, kTile128x64, kTile160x64, kTile64x128, kTile96x128, kTile160x128,
   kTile128x128, kTile128x192, kTile128x256, kTile256x224, kTile256x256, kTileShapes
@@ -759,15 +763,20 @@ struct TilePick {
 constexpr int kTileM[kTileShapes] = {64, 96, 128, 160, 64, 96, 160, 128, 128, 128, 256, 256};
 constexpr int kTileN[kTileShapes] = {64, 64, 64, 64, 128, 128, 128, 128, 192, 256, 224, 256};
 constexpr int kTileNs[kTileShapes] = {320, 385, 436, 517, 480, 577, 676, 615, 750, 830, 1180, 1240};
-static TilePick pick_tile(int M, int ncols, int K, int groups, int max_slices) {
+// columns of a slice: whole tiles
+static int tile_ld(int shape, int ncols) {
+  return (ncols + kTileN[shape] - 1) / kTileN[shape] * kTileN[shape];
+}
+static TilePick pick_tile(int M, int ncols, int K, int groups, size_t floats) {
   const long nch = K / 64;
   const double wbytes = 2.0 * groups * ncols * K;
   TilePick best{kTile128x128, 1};
   double cost = 1e30;
   for (int t = M <= kGemmMaxRows ? 0 : kTileFirstMany; t < kTileShapes; ++t) {
     if (t < kTileFirstMany && M > kTileM[t]) continue;
-    for (int ks = 1; ks <= max_slices; ++ks) {
-      if (ks > 1 && nch / ks < 8) break;  // at least 8 chunks of K per slice
+    const size_t slice = (size_t)M * tile_ld(t, ncols);
+    for (int ks = 1; ks <= kMaxSlices; ++ks) {
+      if (ks > 1 && (nch / ks < 8 || ks * slice > floats)) break;  // at least 8 chunks of K per slice
       const long wgs = (long)((M + kTileM[t] - 1) / kTileM[t]) * groups * ((ncols + kTileN[t] - 1) / kTileN[t]) * ks;
       const double rounds = (double)((wgs + 255) / 256);
       // ns: a full chip runs at about 1 / 1.2 of the rate above, the weights
@@ -826,9 +835,6 @@ static hipError_t launch_tile(const TilePick &p, const bf16_t *A, int lda, int M
 #undef FE_TILE
   return hipGetLastError();
 }
-
-// split-K slices the reductions sum (k_splitk_finish, k_resid_rows)
-constexpr int kMaxSlices = 8;
 
 // Split-K reduction: sums the ks partial slices of a 16-column span in a fixed
 // order and hands the span to the epilogue, like k_gemm_mid would.  A thread
@@ -2026,20 +2032,13 @@ constexpr int kTileNtw = 2, kTileWn = 2, kTileStages = 3, kTileRows = 64 * (4 / 
 template <class Epi>
 static hipError_t rows_unsplit(const bf16_t *A, int lda, int M, int K, const Epi &e, hipStream_t s) {
   if (K % 64 == 0)
-    return launch_tile<Epi, false, false>(pick_tile(std::max(M, kGemmMaxRows + 1), e.nvcols, K, 1, 1), A,
+    return launch_tile<Epi, false, false>(pick_tile(std::max(M, kGemmMaxRows + 1), e.nvcols, K, 1, 0), A,
                                           lda, M, K, e, 1, nullptr, 0, s);
   const dim3 grid((e.nvcols + kTileCols - 1) / kTileCols, 1, (M + kTileRows - 1) / kTileRows);
   hipLaunchKernelGGL((k_gemm_mid<bf16_t, kTileNtw, kTileWn, kTileStages, Epi>), grid, dim3(256), 0, s,
                      A, lda, kDenseRows, M, K, e, nullptr, 0);
   return hipGetLastError();
 }
-// slices of M rows x ncols columns (padded to the tile) that the scratch holds
-static int rows_max_slices(const SplitScratch *ss, int M, int ncols) {
-  if (!ss || !ss->p) return 1;
-  const size_t n = ss->floats / ((size_t)M * ((ncols + 255) / 256 * 256));
-  return n < 1 ? 1 : (int)(n < (size_t)kMaxSlices ? n : kMaxSlices);
-}
-
 hipError_t gemm_store_rows(const void *A, int lda, int M, int K, const void *W, int ncols, void *out,
                            int ldo, const void *embed, const int32_t *tokens, int vocab,
                            void *gather_out, int ld_gather, int d, hipStream_t s,
@@ -2051,9 +2050,9 @@ hipError_t gemm_store_rows(const void *A, int lda, int M, int K, const void *W, 
                                                         (bf16_t *)gather_out, ld_gather, d, M};
   e.lda = lda;
   if (K % 64 == 0 && ncols % 8 == 0 && ss && ss->p) {
-    const TilePick p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
-    if (p.ks > 1 || M <= kGemmMaxRows) {
-      const int ldp = (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape];
+    const TilePick p = pick_tile(M, ncols, K, 1, ss->floats);
+    const int ldp = tile_ld(p.shape, ncols);
+    if (p.ks > 1 || (M <= kGemmMaxRows && (size_t)M * ldp <= ss->floats)) {
       const hipError_t err = launch_tile<EpiStore<bf16_t>, true, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
                                                                  ss->p, ldp, s);
       if (err != hipSuccess) return err;
@@ -2083,10 +2082,11 @@ hipError_t gemm_resid_rows(const void *A, int lda, int M, int K, const void *W, 
   if (ncols > 8192 || ncols % 4) return hipErrorInvalidValue;
   SplitOut so;
   TilePick p{kTile128x128, 1};
-  if (K % 64 == 0) p = pick_tile(M, ncols, K, 1, rows_max_slices(ss, M, ncols));
-  if (p.ks > 1 || (K % 64 == 0 && M <= kGemmMaxRows && ss && ss->p)) {
+  const size_t floats = ss && ss->p ? ss->floats : 0;
+  if (K % 64 == 0) p = pick_tile(M, ncols, K, 1, floats);
+  if (p.ks > 1 || (K % 64 == 0 && M <= kGemmMaxRows && (size_t)M * tile_ld(p.shape, ncols) <= floats)) {
     const EpiResid<bf16_t> e{(const bf16_t *)W, K, ncols, out, ldo, resid, ldr, nullptr, 1, 0, GainCopies{}};
-    so = SplitOut{ss->p, (ncols + kTileN[p.shape] - 1) / kTileN[p.shape] * kTileN[p.shape], p.ks};
+    so = SplitOut{ss->p, tile_ld(p.shape, ncols), p.ks};
     const hipError_t err = launch_tile<EpiResid<bf16_t>, true, true>(p, (const bf16_t *)A, lda, M, K, e, 1,
                                                                ss->p, so.ldp, s);
     if (err != hipSuccess) return err;
@@ -2134,7 +2134,7 @@ hipError_t gemm_kv_rows(const void *A, int lda, long a_layer_stride, int M, int 
     return hipGetLastError();
   }
   if (layers[0].d % 64 == 0) {
-    const TilePick p = pick_tile(M, e.nvcols, layers[0].d, nlayers, 1);
+    const TilePick p = pick_tile(M, e.nvcols, layers[0].d, nlayers, 0);
     e.g.nblocks = (M + kTileM[p.shape] - 1) / kTileM[p.shape];
     return launch_tile<TileKv, false, true>(p, (const bf16_t *)A, lda, M, layers[0].d, e, nlayers, nullptr, 0, s);
   }
