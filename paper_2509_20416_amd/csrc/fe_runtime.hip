@@ -145,11 +145,13 @@ Layout layout_of(const fe_config &c) {
 // Workspace of fe_kv_update for chunks of C rows: the fused inputs, x_0 in
 // fp32, its per-layer RMSNorm (bf16: every layer's rows side by side, for the
 // one K/V launch over all layers), the rows' sums of squares for the fused
-// norm of chunks up to kFusedRows rows, and split-K slices for the 256-row
-// launches.  Chunks of more rows than one such launch takes (bf16) run the
-// fusion and input FCs as 2-D tiled GEMMs; below that the split-K launches
-// are faster (measured on the 8B shapes: 192 rows 205 against 278 us, 256
-// rows 219 against 287 us).
+// norm of chunks up to kFusedRows rows, and the split-K slices of a chunk's
+// GEMMs.  bf16 chunks above kFusedRows rows run the fusion and input FCs over
+// 2-D tiles with a pass over the rows after each; a d that is no multiple of
+// the tiles' 64-wide K chunk, and the self context, whose layers then run as
+// the pass's launches, do so only from kTiledRows rows, where one tiled launch
+// takes more rows than those (8B shapes, 147 rows: 115 us on tiles, 135 with
+// the pass's launches).
 constexpr int kTiledRows = kGemmMaxRows + 1, kFusedRows = 16;
 // rows of a bf16 prefill step from which the attention runs over tiles of rows
 // (k_attn_tile): one workgroup streams a tile's keys, so fewer rows leave the
