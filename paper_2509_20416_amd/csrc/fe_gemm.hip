@@ -1812,9 +1812,22 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
   // whole rounds of CUs, those with one more set the time (5120 columns: 320
   // workgroups on 256 CUs, 12 rows: 2.8 TB/s against 4.3 for 4096 columns).
   // Split-K slices spread the columns evenly for a finish launch of about 6 us,
-  // which the lost share of the stream (at 4.3 TB/s) has to exceed.
+  // which the lost share of the stream (at 4.3 TB/s) has to exceed.  Without
+  // room for two slices (a workspace for at most 16 rows holds none) k_gemm stays.
   bool uneven = false;
-  if (sizeof(T) == 2 && mt == 1 && splittable) {
+  int ks = 1, ldp = 0;  // slices of the launches below: 128-column tiles
+  if (splittable) {
+    constexpr int KC = 8 * Elt<T>::kPer16B;
+    const int gx = (epi.nvcols + 127) / 128, nchk = (K + KC - 1) / KC;
+    // about one workgroup per CU (k_splitk_finish sums at most 8 slices); many
+    // rows make each slice heavier and its partial sums larger: fewer slices
+    ks = min(M > 128 ? 4 : kSliceCap32, max(1, kSliceWgs / gx));
+    ks = min(ks, kMaxSlices);
+    ks = min(ks, max(1, nchk / 4));  // a few chunks per slice for the ring
+    ldp = gx * 128;
+    if ((size_t)ks * M * ldp > ss->floats) ks = 1;
+  }
+  if (sizeof(T) == 2 && mt == 1 && ks > 1) {
     const double fill = (double)grid / ((grid + 255) / 256 * 256);
     uneven = 2.0 * epi.nvcols * K / 4.3e6 * (1.0 / fill - 1.0) > 6.0;
   }
@@ -1878,21 +1891,7 @@ static hipError_t run_gemm(const T *A, int lda, const ARows &arows, int M, int K
   // the re-reading of A that 32-column tiles cost) and K split over enough
   // workgroups to cover the CUs; the fp32 slices are summed, in a fixed order,
   // by a second launch that runs the epilogue.
-  int ks = 1;
-  float *sp = nullptr;
-  int ldp = 0;
-  if (splittable) {
-    constexpr int KC = 8 * Elt<T>::kPer16B;
-    const int gx = (epi.nvcols + 127) / 128, nchk = (K + KC - 1) / KC;
-    // about one workgroup per CU (k_splitk_finish sums at most 8 slices); many
-    // rows make each slice heavier and its partial sums larger: fewer slices
-    ks = min(M > 128 ? 4 : kSliceCap32, max(1, kSliceWgs / gx));
-    ks = min(ks, kMaxSlices);
-    ks = min(ks, max(1, nchk / 4));  // a few chunks per slice for the ring
-    ldp = gx * 128;
-    if ((size_t)ks * M * ldp > ss->floats) ks = 1;
-    if (ks > 1) sp = ss->p;
-  }
+  float *sp = ks > 1 ? ss->p : nullptr;
 #define FE_GEMM_MID_RT(NTWV, WNV, SV, RTV)                                                           \
   hipLaunchKernelGGL((k_gemm_mid<T, NTWV, WNV, SV, Epi, RTV>),                                      \
                      dim3((epi.nvcols + 16 * NTWV * WNV - 1) / (16 * NTWV * WNV), ks), dim3(256), 0,  \

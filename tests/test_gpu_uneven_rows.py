@@ -1,7 +1,8 @@
 """Passes of 5 to 16 sequences whose hidden width leaves the 16-column
 workgroups of the FCs uneven over the compute units (4128 columns: 258
 workgroups): their GEMMs run as K slices with a finish launch, K ragged in
-64-wide chunks."""
+64-wide chunks (16 sequences), or stay whole where the workspace, made for at
+most 16 rows of the two layers, holds no slices (5 sequences)."""
 import numpy as np
 import pytest
 
