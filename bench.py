@@ -215,17 +215,20 @@ def kv_update_cost(cfg, M):
 
 def kv_update_cost_self(cfg, positions):
     """Algorithmic FLOPs and bytes of one cache update under the self context
-    (the N layers run over the rows): per row the fusion and input FCs and per
-    layer Q/K/V, O, gate/up and down, plus the attention's two contractions
-    over the row's p earlier keys and its own; every weight matrix the layers
-    use read once, each row's features, embedding row and written K/V rows."""
+    (the N layers run over the rows): per row the fusion and input FCs, per
+    layer but the last Q/K/V, O, gate/up and down, plus the attention's two
+    contractions over the row's p earlier keys and its own, and the last
+    layer's K/V projections (nothing reads its output); every weight matrix
+    that takes part read once, each row's features, embedding row and written
+    K/V rows."""
     es = 2 if cfg.dtype == "bf16" else 4
     d, F, N, I = cfg.hidden, cfg.n_feat_levels, cfg.n_layers, cfg.intermediate
     qd, kvd = cfg.n_q_heads * cfg.head_dim, cfg.n_kv_heads * cfg.head_dim
     M = len(positions)
-    per_row_mac = F * d * d + 2 * d * d + N * (d * (qd + 2 * kvd) + qd * d + 3 * d * I)
-    attn = sum(N * 4 * qd * (int(p) + 1) for p in positions)
-    wbytes = (F * d * d + 2 * d * d + N * (d * (qd + 2 * kvd) + qd * d + 3 * d * I)) * es
+    per_row_mac = (F * d * d + 2 * d * d + (N - 1) * (d * (qd + 2 * kvd) + qd * d + 3 * d * I)
+                   + 2 * d * kvd)
+    attn = sum((N - 1) * 4 * qd * (int(p) + 1) for p in positions)
+    wbytes = per_row_mac * es
     rbytes = M * (F * d + d + N * 2 * kvd) * es
     return 2 * M * per_row_mac + attn, wbytes + rbytes
 
