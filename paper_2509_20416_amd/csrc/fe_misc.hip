@@ -437,8 +437,8 @@ hipError_t accept_greedy(int B, int N, int k, const int32_t *tokens, const int32
 // time.  Bound by the dependent passes of one CU, so by the instructions a pass
 // issues per id: a row pass tests a lane's four ids against one mask word and
 // adds the unmapped ones only (Z adds the gathered mapped values), a rejection
-// rewrites nothing (8 sequences at the 8B vocabularies: 93 us with a sum, a
-// mask test and a last-id update per id and a rewritten residual, 73 so).
+// rewrites nothing (8 sequences at the 8B vocabularies: 99 us with a sum, a
+// mask test and a last-id update per id and a rewritten residual, 70 so).
 // Every decision is taken on block-reduced values, so control flow is
 // uniform across the workgroup.
 // ---------------------------------------------------------------------------
@@ -447,11 +447,28 @@ constexpr int kAccBatch = 32;  // floats per lane in flight in a pass over a tar
 constexpr int kAccMaxV = kAccSampleMaxV;    // draft ids whose residual fits the LDS
 constexpr int kAccMaxVt = kAccSampleMaxVt;  // target ids the LDS bitmask covers
 constexpr int kAccWaves = kAccThreads / 64;
+// weight of the children not yet rejected, relative to the largest, below which
+// they are not tested (C stays finite: it grows by Z over this weight)
+constexpr float kAccMinWeight = 1e-20f;
 
-__device__ __forceinline__ float acc_sum(float v, float *red) {
+// Sum over the workgroup.  KEEP: also the waves' own sums into `keep`.  READ:
+// also the sum of what `keep` holds, into *kept, read between the two barriers,
+// so that a wave may write its entry again once it has returned.
+template <bool KEEP = false, bool READ = false>
+__device__ __forceinline__ float acc_sum(float v, float *red, float *keep = nullptr,
+                                         float *kept = nullptr) {
   v = group_sum<64>(v);
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = v;
+    if constexpr (KEEP) keep[threadIdx.x >> 6] = v;
+  }
+  if constexpr (READ) {
+    float k = 0.f;
+#pragma unroll
+    for (int w = 0; w < kAccWaves; ++w) k += keep[w];
+    *kept = k;
+  }
   __syncthreads();
   float t = 0.f;
 #pragma unroll
@@ -617,7 +634,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
   constexpr int W = VEC ? 4 : 1;  // target ids per lane per load
   __shared__ float s_rd[kAccMaxV];
   __shared__ uint32_t s_img[kAccMaxVt / 32];
-  __shared__ float red[kAccWaves];
+  __shared__ float red[kAccWaves], s_qw[kAccWaves];
   __shared__ int s_path[kMaxLayers + 1];
   __shared__ int s_cd[kMaxTopk], s_ord[kMaxTopk];
   __shared__ float s_cn[kAccWaves];
@@ -773,22 +790,22 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
       zr[j] = expf(zr[j] - mx);  // 0 past V
       se += zr[j];
     }
-    const float S = acc_sum(se, red);
-    float R = 0.f;  // q mass of the rejected children
+    float Qw = acc_sum<true>(se, red, s_qw);  // weight of q's ids that are not rejected
     // The residual after rejections is (p - C q)^+ with one growing C: each
     // one subtracts a multiple of q and clips at 0, and clipping in between or
     // at the end is the same.  So s_rd keeps p until the last child is
-    // rejected, and a rejection is one sum of min(p, C q), the mass that has
-    // gone.  (C counts in units of exp(z / T - mx).)
+    // rejected.  C and Qw count in units of exp(z / T - mx).  Qw is summed anew
+    // by the wave that holds the rejected id (s_qw: the waves' sums), since
+    // 1 - (the rejected share) is all rounding once the rejected children hold
+    // nearly all of q (a top logit 17 above the rest).
     float C = 0.f;
-    const float Z0 = Z;
-    bool took = false;
+    bool took = false, cut = false;
     for (int j = 0; j < k; ++j) {
       const int rho = s_ord[j];
       const int child = 1 + (lvl - 1) * k + rho;
       const int vd = s_cd[rho];
-      const float e0v = expf(s_zc[rho] - mx), q0v = e0v / S;
-      const float qi = draft_draws.on() ? q0v / (1.f - R) : 1.f;
+      const float e0v = expf(s_zc[rho] - mx);
+      const float qi = draft_draws.on() ? e0v / Qw : 1.f;
       const float rx = draft_draws.on() ? fmaxf(s_rd[vd] - C * e0v, 0.f) : s_rd[vd];
       const float ut = s_uc[j];
       ++t;
@@ -806,24 +823,38 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
         __syncthreads();
         continue;
       }
-      // r <- (r - Z q_i)^+.  A rejected x had r(x) / Z < q_i(x), so its r is
-      // now 0 and stays 0 as C grows: leaving x out of q changes nothing
-      // further but the renormalisation 1 / (1 - R).
-      C += Z / (1.f - R) / S;
-      float dec = 0.f;
+      // r <- (r - Z q_i)^+, and x leaves q.  A rejected x had r(x) / Z < q_i(x),
+      // so its r is 0 from here on: its weight becomes infinite.
+      C += Z / Qw;
+      cut = true;
+      if (wave == ((vd % kAccThreads) >> 6)) {
+        float q = 0.f;
+#pragma unroll
+        for (int jj = 0; jj < kZ; ++jj) {
+          if (tid + jj * kAccThreads == vd) zr[jj] = INFINITY;
+          q += zr[jj] < INFINITY ? zr[jj] : 0.f;
+        }
+        q = group_sum<64>(q);
+        if (lane == 0) s_qw[wave] = q;
+      }
+      float r = 0.f;
 #pragma unroll
       for (int jj = 0; jj < kZ; ++jj) {
         const int v = tid + jj * kAccThreads;
-        dec += v < V ? fminf(s_rd[v], C * zr[jj]) : 0.f;
+        r += v < V ? fmaxf(s_rd[v] - C * zr[jj], 0.f) : 0.f;
       }
-      Z = Z0 - acc_sum(dec, red);
-      R += q0v;
+      Z = acc_sum<false, true>(r, red, s_qw, &Qw);
+#pragma unroll
+      for (int w = 0; w < kAccWaves; ++w) Z += s_cn[w];  // the ids q does not reach
+      // The untested children hold next to nothing of q: testing them would
+      // only divide by that.  The draw from the residual is as exact.
+      if (!(Qw > kAccMinWeight)) break;
     }
     if (took) {
       __syncthreads();  // s_rd, s_ord and the children are read before they change
       continue;
     }
-    if (C > 0.f) {  // the residual that the draw takes from
+    if (cut) {  // the residual that the draw takes from
 #pragma unroll
       for (int j = 0; j < kZ; ++j) {
         const int v = tid + j * kAccThreads;
