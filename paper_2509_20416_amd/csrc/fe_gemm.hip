@@ -288,7 +288,9 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const T *__restrict__ A, int ld
   __shared__ float s_inv[MR];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rq = lane >> 4, l16 = lane & 15;
   const int c0 = blockIdx.x * SPAN;
-  const int kpad = (K + PE - 1) / PE * PE;
+  // unsigned: a signed division by the runtime xper below is twice the
+  // instructions, all of them ahead of the input rows' loads
+  const unsigned kpad = ((unsigned)K + PE - 1) / PE * PE;
   const int npc = kpad / PE;  // 16-byte pieces per lane per row
   T *xs = reinterpret_cast<T *>(xs_raw);
 
@@ -308,13 +310,17 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const T *__restrict__ A, int ld
   for (int i = 0; i < kGvDepth; ++i) ba[i] = ldw(min(i, npc - 1));
 
   constexpr int XPT = kGvMaxLds / 16 / NTHR;  // input pieces per thread, at most
-  const int xper = kpad / E, xtot = MR * xper;
+  const unsigned xper = kpad / E;
+  const int xtot = MR * xper;
+  // input piece idx: row m, elements e .. of it
+  auto xrow = [&](int idx) { return MR == 1 ? 0 : (int)((unsigned)idx / xper); };
+  auto xel = [&](int idx) { return (MR == 1 ? idx : (int)((unsigned)idx % xper)) * E; };
   u32x4 xr[XPT];
 #pragma unroll
   for (int u = 0; u < XPT; ++u)
     if (NTHR * u < xtot) {  // uniform: batch u holds at least one piece
       const int idx = min(tid + NTHR * u, xtot - 1);
-      const int m = idx / xper, e = min((idx % xper) * E, K - E);
+      const int m = xrow(idx), e = min(xel(idx), K - E);
       xr[u] = *reinterpret_cast<const u32x4 *>(A + (size_t)arows.row(min(m, M - 1)) * lda + e);
     }
 
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(64 * W) void k_gemv(const T *__restrict__ A, int ld
   for (int u = 0; u < XPT; ++u) {
     const int idx = tid + NTHR * u;
     if (NTHR * u < xtot && idx < xtot) {
-      const int m = idx / xper, e = (idx % xper) * E;
+      const int m = xrow(idx), e = xel(idx);
       *reinterpret_cast<u32x4 *>(xs + (size_t)m * kpad + e) = (m < M && e < K) ? xr[u] : zero;
     }
   }
