@@ -1603,8 +1603,9 @@ template <typename T> struct EpiLm {
 
   // Selection key of tempered logit x: x, or with draws x + Gumbel(u) = x -
   // log(-log(u)) (sampling without replacement).  Ordered as 32-bit integers:
-  // 0 is no candidate, 1 a NaN (listed after every number for up to 16 rows,
-  // else no candidate), the rest the order-preserving bits of the float.
+  // 0 is no candidate, 1 a NaN, the rest the order-preserving bits of the
+  // float.  Up to 16 rows list -inf (a draw of u = 0) and NaN, after every
+  // other key; above, neither is a candidate.
   __device__ void finish(float *tile, int ldt, int M, int c0, int span, const Pre &) const {
     // with more items than one round of the waves, two at a time: a round's
     // maxima are a chain, and the other item's fill its gaps
@@ -1617,7 +1618,7 @@ template <typename T> struct EpiLm {
     const int l16 = lane & 15, base = lane & 48;
     const int nseg = span >> 6, items = M * nseg, ntile = (nvcols + 63) >> 6;
     const bool vec = aligned16(a.logits), gen = a.draws.so != nullptr, on = a.draws.on();
-    const uint32_t nan_key = M <= 16 ? 1u : 0u;
+    const uint32_t nan_key = M <= 16 ? 1u : 0u, ninf_key = M <= 16 ? 0x007fffffu : 0u;
     const uint64_t seed = gen ? a.draws.so[0] : 0, offset = gen ? a.draws.so[1] : 0;
     for (int i0 = 4 * U * wave; i0 < items; i0 += 4 * U * nw) {
       float v[U][4], mx[U], se[U];
@@ -1671,7 +1672,8 @@ template <typename T> struct EpiLm {
         for (int q = 0; q < 4; ++q) {
           const float kf = on ? v[u][q] - logf(-logf(n[q])) : v[u][q];
           const uint32_t w = __float_as_uint(kf);
-          key[u][q] = !ok ? 0u : kf != kf ? nan_key : (w & 0x80000000u) ? ~w : (w | 0x80000000u);
+          const uint32_t low = kf != kf ? nan_key : ninf_key;
+          key[u][q] = !ok ? 0u : !(kf > -INFINITY) ? low : (w & 0x80000000u) ? ~w : (w | 0x80000000u);
         }
       }
       uint32_t got[U];  // lane r: the r-th best key, its column and its z / T
