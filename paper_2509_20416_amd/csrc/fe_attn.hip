@@ -26,6 +26,7 @@
 //    result does not depend on scheduling.  A sequence with an empty prefix
 //    still runs chunk 0 for its cascade keys.
 #include "fe_attn_unit.h"
+#include <algorithm>
 
 namespace fe {
 
@@ -492,27 +493,68 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 // merges; tiles of 128 columns took 52 us with four waves (two column tiles
 // each) and 46 us with eight, because a prompt's last tile sees twice the
 // average keys and only two small workgroups per CU even that out.
-constexpr int kTileQ = 64, kTileWaves = 4;
+//
+// A workgroup walks a tile's keys by itself, 0.7 us a stage, so a long history
+// behind few tiles (few rows or KV heads, or one sequence longer than the rest)
+// left most CUs idle behind it.  Such tiles are cut into pieces of keys, a
+// workgroup each, whose partial sums k_attn_tile_merge adds.  The plan decides
+// on the device, where the histories are known: all tiles stay whole where the
+// longest takes at most twice what the launch's stages are per resident
+// workgroup (the short tiles then fill its time), or at most kWholeStages.
+// Updates of three 1024-wide layers, us a call (row by row / whole tiles / cut):
+// 64 rows after 8192 keys, one KV head of 8 query heads 297 / 549 / 209, 8 KV
+// heads of 4 696 / 559 / 229; 256 rows of which one sequence has 8192 keys and
+// the others 64, 8 KV heads of 4 551 / 654 / 327; 64 rows with no history 253 /
+// 180 / 185: the merge's launch finds nothing to do there, 2 to 4 us a layer.
+// (The last piece to be done adding the sums saved that launch, but a release
+// fence per piece writes back the L2: 292 where the launch gives 229.)
+constexpr int kTileQ = 64, kTileWaves = 4, kTileKeys = 32;
+constexpr int kPieceStages = 16, kWholeStages = 32;  // shortest piece, longest tile never cut
+constexpr int kTilePieces = 64;                      // pieces of one tile, at most
+static_assert(kTilePlanSplit * 2 == kTilePlanPieces, "a cut tile has fewer than 2 nst / L pieces");
 
-// The tiles: tiles[0] their number, tile i rows tiles[1 + i] .. tiles[2 + i] - 1.
-// A tile is at most tq consecutive rows of one run: rows with the same
-// start whose ranges are valid (an invalid row is a tile of its own).  One
-// workgroup; two scans (the run's first row, the tile's index) per 1024 rows.
-__global__ __launch_bounds__(1024) void k_attn_tile_plan(const int32_t *__restrict__ ranges, int M,
-                                                         int pmax, int tq,
-                                                         int32_t *__restrict__ tiles) {
-  __shared__ int s_w[16], s_carry[2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  auto bad = [&](int m) {
-    const int P = ranges[2 * m + 1] - ranges[2 * m];
-    return P < 0 || P > pmax;
-  };
-  if (tid == 0) s_carry[0] = s_carry[1] = 0;
+// Inclusive sum of x over the workgroup's 1024 threads; the last one's in total.
+__device__ __forceinline__ int plan_scan(int x, int *s_w, int &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
   __syncthreads();
+  if (lane == 63) s_w[wave] = x;
+  __syncthreads();
+  total = 0;
+  for (int w = 0; w < 16; ++w) {
+    if (w < wave) x += s_w[w];
+    total += s_w[w];
+  }
+  return x;
+}
+
+// The plan (TilePlan) of rows that see keys ranges[2m] .. ranges[2m + 1] - 1.  A
+// tile is at most tq consecutive rows of one run: rows with the same
+// start whose ranges are valid (an invalid row is a tile of its own).  One
+// workgroup; per 1024 rows a scan for the run's first row and one for the
+// tile's index, and where tiles are cut three per 1024 tiles for the lists.
+// `slots`: partial results the scratch has room for (0: no tile is cut).
+__global__ __launch_bounds__(1024) void k_attn_tile_plan(const int32_t *__restrict__ ranges, int M,
+                                                         int pmax, int tq, int ncols, int slots,
+                                                         int wgs, int32_t *__restrict__ plan) {
+  __shared__ int s_w[16], s_carry[2], s_max[16], s_stg[1025];
+  __shared__ long s_sum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const TilePlan pl{plan, M};
+  int32_t *tiles = pl.first(), *stg = pl.stages();
+  if (tid == 0) s_carry[0] = s_carry[1] = 0;
   for (int m0 = 0; m0 < M; m0 += 1024) {
-    const int m = m0 + tid;
-    bool first = m < M;
-    if (m > 0 && m < M) first = bad(m) || bad(m - 1) || ranges[2 * m] != ranges[2 * m - 2];
+    const int m = m0 + tid, mc = min(m, M - 1), mp = max(mc - 1, 0);
+    const int start = ranges[2 * mc], P = ranges[2 * mc + 1] - start;
+    const int start0 = ranges[2 * mp], P0 = ranges[2 * mp + 1] - start0;
+    const bool bad = P < 0 || P > pmax, bad0 = P0 < 0 || P0 > pmax;
+    const bool first = m < M && (m == 0 || bad || bad0 || start != start0);
+    s_stg[tid + 1] = 0;
+    if (tid == 0) s_stg[0] = 0;
     // the run's first row: the largest row <= m that starts one
     int x = first ? m : 0;
 #pragma unroll
@@ -524,26 +566,96 @@ __global__ __launch_bounds__(1024) void k_attn_tile_plan(const int32_t *__restri
     __syncthreads();
     x = max(x, s_carry[0]);
     for (int w = 0; w < wave; ++w) x = max(x, s_w[w]);
-    __syncthreads();
     const bool head = m < M && (m - x) % tq == 0;
-    const uint64_t vote = __ballot(head);
-    if (lane == 63) s_w[wave] = __popcll(vote);
-    __syncthreads();
-    int idx = s_carry[1] + __popcll(vote & ((1ull << lane) - 1));
-    int total = 0;
-    for (int w = 0; w < 16; ++w) {
-      if (w < wave) idx += s_w[w];
-      total += s_w[w];
-    }
-    if (head) tiles[1 + idx] = m;
+    const int before = s_carry[1];  // tiles of the rounds before; the last of them may go on
+    int total;
+    const int idx = plan_scan(head ? 1 : 0, s_w, total);  // the row's tile is before + idx - 1
+    if (head) tiles[before + idx - 1] = m;
+    if (m < M && !bad) atomicMax(&s_stg[idx], (P + kTileKeys - 1) / kTileKeys);
     __syncthreads();
     if (tid == 1023) s_carry[0] = x;
-    if (tid == 0) s_carry[1] += total;
+    if (tid < total) stg[before + tid] = s_stg[tid + 1];
+    if (tid == 0) {
+      s_carry[1] = before + total;
+      if (before > 0) stg[before - 1] = max(stg[before - 1], s_stg[0]);
+    }
     __syncthreads();
   }
+  const int nt = s_carry[1];
+  if (tid == 0) tiles[nt] = M;
+  // the tiles' stages: their sum and the largest
+  long sum = 0;
+  int most = 0;
+  if (slots > 0) {
+    for (int t = tid; t < nt; t += 1024) {
+      sum += stg[t];
+      most = max(most, stg[t]);
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+      sum += __shfl_xor(sum, o, 64);
+      most = max(most, __shfl_xor(most, o, 64));
+    }
+    if (lane == 0) {
+      s_sum[wave] = sum;
+      s_max[wave] = most;
+    }
+  }
+  __syncthreads();
+  if (slots > 0) {
+    sum = 0;
+    most = 0;
+    for (int w = 0; w < 16; ++w) {
+      sum += s_sum[w];
+      most = max(most, s_max[w]);
+    }
+    sum *= ncols;
+  }
+  // stages of a piece: an even share of the work or more, so that fewer than
+  // kTilePlanSplit tiles are cut, into at most kTilePlanPieces pieces; at most
+  // `slots` of them (a tile that is cut has n > L stages and ceil(n / L) <=
+  // 2 n / L pieces)
+  const long share = (sum + wgs - 1) / wgs;
+  const bool cuts = most > kWholeStages && most > 2 * share;
+  int ne = nt, ns = 0;
+  if (!cuts) {
+    // the last tile first (a prompt's last tiles see the most keys)
+    for (int j = tid; j < nt; j += 1024) {
+      const int t = nt - 1 - j, row0 = tiles[t];
+      pl.pieces()[j] = int4{row0, tiles[t + 1] - row0, 0, stg[t]};
+    }
+  } else {
+    const long room = (2 * sum + slots - 1) / slots;
+    long want = share > kPieceStages ? share : kPieceStages;
+    want = want > room ? want : room;
+    const int fewest = (most + kTilePieces - 1) / kTilePieces;
+    const int L = want > most ? most : max((int)want, fewest);
+    int nslot = 0;
+    ne = 0;
+    for (int j0 = 0; j0 < nt; j0 += 1024) {
+      const int t = nt - 1 - (j0 + tid);
+      const int n = t >= 0 ? stg[t] : 0, np = t < 0 ? 0 : n > L ? (n + L - 1) / L : 1;
+      const bool cut = np > 1;
+      int te, tsl, ts;
+      const int e = ne + plan_scan(np, s_w, te) - np;
+      const int sl = nslot + plan_scan(cut ? np : 0, s_w, tsl) - (cut ? np : 0);
+      const int si = ns + plan_scan(cut ? 1 : 0, s_w, ts) - (cut ? 1 : 0);
+      if (t >= 0) {
+        const int row0 = tiles[t], rows = tiles[t + 1] - row0;
+        // stages n / np each, one more in the first n % np
+        const int each = n / np, more = n % np;
+        for (int k = 0; k < np; ++k)
+          pl.pieces()[e + k] = int4{row0, rows | (cut ? sl + k + 1 : 0) << 8, k * each + min(k, more),
+                                    each + (k < more ? 1 : 0)};
+        if (cut) pl.cut()[si] = int4{row0, rows, sl, np};
+      }
+      ne += te;
+      nslot += tsl;
+      ns += ts;
+    }
+  }
   if (tid == 0) {
-    tiles[0] = s_carry[1];
-    tiles[1 + s_carry[1]] = M;
+    plan[0] = ne;
+    plan[1] = ns;
   }
 }
 
@@ -551,15 +663,16 @@ template <int D, int GH>
 __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *__restrict__ Kc,
                                                       const bf16_t *__restrict__ Vc,
                                                       const int32_t *__restrict__ ranges,
-                                                      const int32_t *__restrict__ tiles,
+                                                      const int32_t *__restrict__ plan, int M,
                                                       const float *__restrict__ q,
                                                       const float *__restrict__ knew,
                                                       const float *__restrict__ vnew,
-                                                      bf16_t *__restrict__ out, int Hq, int Hkv,
+                                                      bf16_t *__restrict__ out,
+                                                      float *__restrict__ parts, int Hq, int Hkv,
                                                       const float *__restrict__ rope, int pmax) {
   constexpr int NKC = D / 32, NDT = D / 16, VPR = D / 8, RB = 2 * D, HD = D / 2;
   constexpr int RPW = 256 / RB, LQ = VPR == 16 ? 3 : 2;
-  constexpr int SK = 32, HALF = SK * RB, STAGE = 2 * HALF, S = 4;
+  constexpr int SK = kTileKeys, HALF = SK * RB, STAGE = 2 * HALF, S = 4;
   constexpr int NL = STAGE / 1024 / kTileWaves;  // 1 KB loads per wave per stage
   constexpr int CT = kTileQ / 16 / kTileWaves;   // 16-column tiles per wave
   static_assert((S - 1) * NL <= 63, "outstanding loads stay within the vmcnt range");
@@ -595,15 +708,16 @@ __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *
   const int voff = HALF + (4 * g + (r >> 2)) * RB + 16 * (((r & 3) >> 1) ^ swz(4 * g + (r >> 2))) + 8 * (r & 1);
   const uint32_t ring0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)&ring[0][0]) + wave * 1024);
-  const int nitems = tiles[0] * ncols;
+  const TilePlan pl{const_cast<int32_t *>(plan), M};
+  const int nitems = plan[0] * ncols;
   // The last tiles of a prompt see the most keys and go first; the second
   // half of the grid, which shares the compute units of the first, takes its
   // items in the opposite order, so a unit gets a long item and a short one.
   const int half = gridDim.x / 2, wg = blockIdx.x;
   const int first = wg < half ? wg : (int)gridDim.x - 1 - (wg - half);
   for (int it = first; it < nitems; it += gridDim.x) {
-    const int t = tiles[0] - 1 - it / ncols, col = it % ncols;
-    const int row0 = tiles[1 + t], n = tiles[2 + t] - row0;
+    const int4 pc = pl.pieces()[it / ncols];
+    const int col = it % ncols, row0 = pc.x, n = pc.y & 255, slot = (pc.y >> 8) - 1, st0 = pc.z, nst = pc.w;
     const int c = col / ngrp, h0 = c * G + (col % ngrp) * GH;
     const int start = ranges[2 * row0];
     // column 16 i + r of this wave: row mrow[i], head mh[i], its prefix length
@@ -636,12 +750,11 @@ __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *
     int Pt = s_p[0];  // keys of the tile
 #pragma unroll
     for (int w = 1; w < kTileWaves; ++w) Pt = max(Pt, s_p[w]);
-    const int nst = (Pt + SK - 1) / SK;
     const bf16_t *kb = Kc + ((size_t)start * Hkv + c) * D, *vb = Vc + ((size_t)start * Hkv + c) * D;
     // stage st (clamped: past the end the last one again, so every wave
     // issues the same count), rows clamped inside the tile's keys
     auto issue = [&](int st) {
-      const int k0 = min(st, nst - 1) * SK;
+      const int k0 = (st0 + min(st, nst - 1)) * SK;
       const uint32_t dst = ring0 + (st % S) * STAGE;
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
@@ -719,7 +832,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
       issue(st + S - 1);
-      const int k0 = st * SK;
+      const int k0 = (st0 + st) * SK;
       if (k0 >= pmx) continue;  // no column of this wave sees this stage
       const unsigned char *ringp = &ring[0][0];
       const int kst = (st % S) * STAGE + koff, vst = (st % S) * STAGE + voff;
@@ -840,12 +953,31 @@ __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *
 #pragma unroll
     for (int i = 0; i < CT; ++i) {
       const float lt = lacc[i].x;  // every row of the product with ones is the column's sum
+      if (slot >= 0 && st0 > 0) {  // a later piece of a cut tile: its sums as they are
+        if (!live[i]) continue;
+        const int cidx = wave * 16 * CT + 16 * i + r;
+        float *ps = parts + ((size_t)slot * ncols + col) * (kTileQ * (D + 2));
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) *reinterpret_cast<f32x4 *>(ps + cidx * D + 16 * dt + 4 * g) = oacc[i][dt];
+        if (g == 0) *reinterpret_cast<float2 *>(ps + kTileQ * D + 2 * cidx) = float2{mx_[i], lt};
+        continue;
+      }
       const float M = fmaxf(mx_[i], sown[i]);
       const float sp = sexp2(mx_[i], M), sc = __builtin_amdgcn_exp2f(sown[i] - M);
       float inv = 1.f / (lt * sp + sc);
       if (bad[i]) inv = __int_as_float(0x7fc00000);  // P outside [0, pmax]
       if (!live[i]) continue;
       const float *vp = vnew + ((size_t)mrow[i] * Hkv + c) * D + 4 * g;
+      if (slot >= 0) {  // the first piece of a cut tile, which takes the own key
+        const int cidx = wave * 16 * CT + 16 * i + r;
+        float *ps = parts + ((size_t)slot * ncols + col) * (kTileQ * (D + 2));
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+          *reinterpret_cast<f32x4 *>(ps + cidx * D + 16 * dt + 4 * g) =
+              oacc[i][dt] * sp + *reinterpret_cast<const f32x4 *>(vp + 16 * dt) * sc;
+        if (g == 0) *reinterpret_cast<float2 *>(ps + kTileQ * D + 2 * cidx) = float2{M, lt * sp + sc};
+        continue;
+      }
       bf16_t *op = out + ((size_t)mrow[i] * Hq + mh[i]) * D + 4 * g;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
@@ -853,6 +985,56 @@ __global__ __launch_bounds__(64 * kTileWaves, 2) void k_attn_tile(const bf16_t *
         *reinterpret_cast<u32x2 *>(op + 16 * dt) = u32x2{pack_bf16(o.x, o.y), pack_bf16(o.z, o.w)};
       }
     }
+  }
+}
+
+// Rows of the cut tiles from their pieces' partials: a thread takes four dims
+// of a (row, head) column, 256 threads a share of a (tile, head group).
+template <int D, int GH>
+__global__ __launch_bounds__(256) void k_attn_tile_merge(const int32_t *__restrict__ plan, int M,
+                                                         const float *__restrict__ parts,
+                                                         bf16_t *__restrict__ out, int Hq, int Hkv) {
+  constexpr int TPC = D / 4, SHARES = kTileQ * TPC / 256, SLOT = kTileQ * (D + 2);
+  const TilePlan pl{const_cast<int32_t *>(plan), M};
+  const int G = Hq / Hkv, ngrp = G / GH, ncols = Hkv * ngrp, units = plan[1] * ncols * SHARES;
+  for (int u = blockIdx.x; u < units; u += gridDim.x) {
+    const int item = u / SHARES, col = item % ncols;
+    const int4 ct = pl.cut()[item / ncols];
+    const int idx = (u % SHARES) * 256 + threadIdx.x, cidx = idx / TPC, e = idx % TPC * 4;
+    if (cidx / GH >= ct.y) continue;
+    const int m = ct.x + cidx / GH, h = col / ngrp * G + col % ngrp * GH + cidx % GH, np = ct.w;
+    const float *ps = parts + ((size_t)ct.z * ncols + col) * SLOT;
+    const size_t step = (size_t)ncols * SLOT;
+    float mx = -INFINITY, L = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    constexpr int R = 8;  // partials per round trip
+    for (int k0 = 0; k0 < np; k0 += R) {
+      f32x4 ov[R];
+      float2 ml[R];
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const float *p = ps + min(k0 + k, np - 1) * step;
+        ov[k] = *reinterpret_cast<const f32x4 *>(p + cidx * D + e);
+        ml[k] = *reinterpret_cast<const float2 *>(p + kTileQ * D + 2 * cidx);
+      }
+      float mn = mx;
+#pragma unroll
+      for (int k = 0; k < R; ++k) mn = fmaxf(mn, ml[k].x);
+      const float old = sexp2(mx, mn);
+      o *= old;
+      L *= old;
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+        if (k0 + k < np) {
+          const float w = sexp2(ml[k].x, mn);
+          o += ov[k] * w;
+          L += ml[k].y * w;
+        }
+      mx = mn;
+    }
+    o *= 1.f / L;
+    *reinterpret_cast<u32x2 *>(out + ((size_t)m * Hq + h) * D + e) =
+        u32x2{pack_bf16(o.x, o.y), pack_bf16(o.z, o.w)};
   }
 }
 
@@ -959,26 +1141,45 @@ int attention_cpw(int B, int Hkv, int ngroups, int nch) {
 // query heads of one column group: the tiles carry kTileQ / GH rows
 static int tile_heads(int G) { return G % 8 == 0 ? 8 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
 
-hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int32_t *tiles,
-                          hipStream_t s) {
+// Partial results that fit behind the plan; none where no history is long
+// enough for a tile to be cut.
+static int tile_slots(int M, int pmax, int D, size_t floats) {
+  if ((pmax + kTileKeys - 1) / kTileKeys <= kWholeStages) return 0;
+  const size_t n = (floats - tile_plan_ints(M)) / ((size_t)kTileQ * (D + 2));
+  return (int)std::min<size_t>(n, kTilePlanPieces);
+}
+
+hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int D,
+                          float *scratch, size_t floats, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_attn_tile_plan, dim3(1), dim3(1024), 0, s, ranges, M, pmax,
-                     kTileQ / tile_heads(Hq / Hkv), tiles);
+  if (floats < tile_plan_ints(M)) return hipErrorInvalidValue;
+  const int GH = tile_heads(Hq / Hkv);
+  hipLaunchKernelGGL(k_attn_tile_plan, dim3(1), dim3(1024), 0, s, ranges, M, pmax, kTileQ / GH, Hq / GH,
+                     tile_slots(M, pmax, D, floats), std::min(resident_waves() / 2, kTilePlanSplit),
+                     (int32_t *)scratch);
   return hipGetLastError();
 }
 
-hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges,
-                           const int32_t *tiles, int M, const float *q, const float *knew,
+hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges, float *scratch,
+                           size_t floats, int M, const float *q, const float *knew,
                            const float *vnew, void *out, int Hq, int Hkv, int D,
                            const float *rope, int pmax, hipStream_t s) {
   if (M <= 0) return hipSuccess;
+  if (floats < tile_plan_ints(M)) return hipErrorInvalidValue;
   const int GH = tile_heads(Hq / Hkv);
-  // two workgroups per CU; each takes every gridDim.x-th (tile, column group)
-  const long items = (long)M * (Hq / GH);
-  const dim3 grid((unsigned)(items < resident_waves() / 2 ? items : resident_waves() / 2));
+  const bool cut = tile_slots(M, pmax, D, floats) > 0;  // the plan may have cut tiles
+  // two workgroups per CU; each takes every gridDim.x-th (piece, head group)
+  const long items = (long)M * (Hq / GH), wgs = resident_waves() / 2;
+  const dim3 grid((unsigned)(cut || items > wgs ? wgs : items));
+  const int32_t *plan = (const int32_t *)scratch;
+  float *parts = scratch + tile_plan_ints(M);
 #define FE_ATTN_TILE(DV, GHV)                                                                     \
-  hipLaunchKernelGGL((k_attn_tile<DV, GHV>), grid, dim3(64 * kTileWaves), 0, s, (const bf16_t *)K,            \
-                     (const bf16_t *)V, ranges, tiles, q, knew, vnew, (bf16_t *)out, Hq, Hkv, rope, pmax)
+  hipLaunchKernelGGL((k_attn_tile<DV, GHV>), grid, dim3(64 * kTileWaves), 0, s, (const bf16_t *)K, \
+                     (const bf16_t *)V, ranges, plan, M, q, knew, vnew, (bf16_t *)out, parts, Hq,  \
+                     Hkv, rope, pmax);                                                             \
+  if (cut)                                                                                         \
+    hipLaunchKernelGGL((k_attn_tile_merge<DV, GHV>), dim3((wgs + 1) / 2), dim3(256), 0, s, plan, M, parts, \
+                       (bf16_t *)out, Hq, Hkv)
 #define FE_ATTN_TILE_D(DV)                 \
   switch (GH) {                            \
     case 8: FE_ATTN_TILE(DV, 8); break;    \

@@ -450,12 +450,32 @@ hipError_t attention(int dt, const void *K, const void *V, Seqs seqs,
 // share their sequence's keys: row m (q [M, Hq, D], own key and value knew /
 // vnew [M, Hkv, D], all unrotated fp32) sees cache rows ranges[2m] ..
 // ranges[2m + 1] - 1 and its own key, at position P = the range's length; a row
-// whose P lies outside [0, pmax] gets a NaN row.  tiles: the plan of the same
-// ranges from attn_tile_plan (at most M tiles: M + 2 ints).
-hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int32_t *tiles,
-                          hipStream_t s);
-hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges,
-                           const int32_t *tiles, int M, const float *q, const float *knew,
+// whose P lies outside [0, pmax] gets a NaN row.  scratch: tile_plan_ints(M)
+// ints of the plan of the same ranges, from attn_tile_plan, and what follows up
+// to `floats` (the same in both calls) for partial results of tiles that the
+// plan cuts; 16-byte aligned.
+constexpr int kTilePlanPieces = 1024, kTilePlanSplit = 512;
+// The plan: [0] the pieces' number, [1] the cut tiles'; a piece is (first row,
+// rows | (1 + partial slot, 0 where the tile is whole) << 8, first stage,
+// stages), a cut tile (first row, rows, first partial slot, pieces); then the
+// tiles' first rows and stages.  Whole tiles are at most M, pieces of cut tiles
+// at most kTilePlanPieces, cut tiles at most kTilePlanSplit.
+struct TilePlan {
+  int32_t *p;
+  int M;
+  __host__ __device__ int4 *pieces() const { return reinterpret_cast<int4 *>(p + 4); }
+  __host__ __device__ int4 *cut() const { return pieces() + M + kTilePlanPieces; }
+  __host__ __device__ int32_t *first() const { return reinterpret_cast<int32_t *>(cut() + kTilePlanSplit); }
+  __host__ __device__ int32_t *stages() const { return first() + M + 1; }
+  __host__ __device__ int32_t *end() const { return stages() + M; }
+};
+inline size_t tile_plan_ints(int M) {
+  return 4 + 4 * ((size_t)M + kTilePlanPieces + kTilePlanSplit) + (2 * (size_t)M + 1 + 3) / 4 * 4;
+}
+hipError_t attn_tile_plan(const int32_t *ranges, int M, int pmax, int Hq, int Hkv, int D,
+                          float *scratch, size_t floats, hipStream_t s);
+hipError_t attention_tiles(const void *K, const void *V, const int32_t *ranges, float *scratch,
+                           size_t floats, int M, const float *q, const float *knew,
                            const float *vnew, void *out, int Hq, int Hkv, int D,
                            const float *rope, int pmax, hipStream_t s);
 // kAttnChunk-key chunks per attention work unit for a launch of B sequences

@@ -154,8 +154,11 @@ Layout layout_of(const fe_config &c) {
 // the pass's launches).
 constexpr int kTiledRows = kGemmMaxRows + 1, kFusedRows = 16;
 // rows of a bf16 prefill step from which the attention runs over tiles of rows
-// (k_attn_tile): one workgroup streams a tile's keys, so fewer rows leave the
-// chip idle where the row-by-row units split each row's keys
+// (k_attn_tile).  The plan and the merge of cut tiles cost about 10 us a call
+// that fewer rows do not win back: three 1024-wide layers, rows after 1000 keys,
+// row by row / tiles: 17 rows 163 / 187 us with 8 KV heads, 154 / 186 with one;
+// 48 rows 207 / 196 and 181 / 200; 63 rows 219 / 204 and 195 / 205 (after 4000
+// keys 432 / 208 and 206 / 205)
 constexpr int kAttnTileRows = 64;
 
 struct UpdLayout {
@@ -1165,12 +1168,12 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
   // bf16 chunks of more rows than one batched launch takes: every GEMM as one
   // 2-D tiled launch over all rows (each weight matrix streamed once per chunk)
   const bool tiled = dt && Mc >= kTiledRows;
-  // the tiles' plan takes the place of the attention partials, which the tiled
-  // attention does not need; a split set by the caller keeps the split kernels
+  // the tiles' plan and partials take the place of the row-by-row attention's
+  // partials; a split set by the caller keeps the split kernels
   const bool attn_tiles = dt && Mc >= kAttnTileRows && h->attn_split == 0 &&
-                          U.part_floats >= (size_t)Mc + 2;
-  int32_t *tiles = (int32_t *)part;
-  if (attn_tiles && c.n_layers > 1) FE_TRY(attn_tile_plan(ranges, Mc, pmax, Hq, Hkv, tiles, s));
+                          U.part_floats >= tile_plan_ints(Mc);
+  if (attn_tiles && c.n_layers > 1)
+    FE_TRY(attn_tile_plan(ranges, Mc, pmax, Hq, Hkv, D, part, U.part_floats, s));
   for (int l = 0; l < c.n_layers; ++l) {
     const Range range("fe.prefill_layer");
     const fe_layer_weights &lw = h->layers[l];
@@ -1205,8 +1208,8 @@ fe_status prefill_layers(fe_drafter *h, const UpdLayout &U, char *ws, int Mc,
     FE_TRY(kv_scatter(dt, knew, vnew, Mc, Hkv, D, positions, dst_rows, (long)cache->rows,
                       c.max_prefix, rope, dt ? 0 : 1, cache->k[l], cache->v[l], s));
     if (attn_tiles)
-      FE_TRY(attention_tiles(cache->k[l], cache->v[l], ranges, tiles, Mc, q, knew, vnew, ao, Hq, Hkv,
-                             D, rope, pmax, s));
+      FE_TRY(attention_tiles(cache->k[l], cache->v[l], ranges, part, U.part_floats, Mc, q, knew, vnew, ao,
+                             Hq, Hkv, D, rope, pmax, s));
     for (int s0 = 0; s0 < Mc && !attn_tiles; s0 += kGemmMaxRows) {
       const int Ms = std::min(kGemmMaxRows, Mc - s0);
       const int cpw = h->attn_split > 0 ? h->attn_split : attention_cpw(Ms, Hkv, 1, nch);

@@ -62,6 +62,49 @@ def test_tiles_match_split_kernels(cfg, acc, plens):
         assert_rows_close(f"array {i}", a[up.dst_rows], b[up.dst_rows], TOL["bf16"])
 
 
+# Histories that are cut into pieces over several workgroups (more than 32
+# stages of 32 keys), next to short ones and to the longest that stay whole;
+# the cut tiles' heights as above, and pieces that most columns of a wave see
+# none of
+LONG = [
+    (SELF(C.SMALL_GQA_BF16), [60, 3, 1, 9], [4200, 0, 1024, 1025]),
+    (SELF(C.SMALL_GQA8_BF16_D128), [9, 70, 1], [2500, 0, 1900]),
+    (SELF(C.SMALL_MHA_BF16_D128), [65, 2], [1100, 3000]),
+    (SELF(C.SMALL_GQA2_BF16), [40, 33], [990, 1023]),
+    (SELF(C.SMALL_GQA_BF16), [1] * 64, [2400] + [20] * 63),
+]
+
+
+@pytest.mark.parametrize("cfg,acc,plens", LONG, ids=[f"{c.name}-{len(a)}x{a[0]}" for c, a, _ in LONG])
+def test_long_ragged_histories_match_oracle(cfg, acc, plens):
+    from tests.test_gpu_kv_update_self import _run
+    acc, plens = np.asarray(acc), np.asarray(plens)
+    cap = int((acc + plens).max())
+    _run(cfg.with_(n_layers=3), make_update_rows(cfg, acc, plens, capacity=cap, seed=16), 1024, max_prefix=cap)
+
+
+@pytest.mark.parametrize("split", [0, 4])
+def test_infinite_values_in_a_history_stay_apart(split):
+    """A cached value row of infinities makes NaN or infinite the rows that see
+    it, in whichever piece of the history it lies, and no other row."""
+    import torch
+    from paper_2509_20416_amd import Drafter
+    from paper_2509_20416_amd.drafter import to_device
+    cfg = SELF(C.SMALL_GQA_BF16).with_(n_layers=2)
+    up = make_update_rows(cfg, np.array([70, 20]), np.array([2000, 2000]), capacity=2100, seed=17)
+    dr = Drafter(cfg, make_weights(cfg, 3), max_batch=1, max_prefix=2100, max_topk=cfg.topk)
+    dr.set_attention_split(split)
+    shape = (up.cache_rows, cfg.n_kv_heads, cfg.head_dim)
+    kv = [[to_device(float_tensor(f"inf.{n}{l}", shape, 5, cfg.dtype), cfg.dtype, dr.device)
+           for l in range(2)] for n in "kv"]
+    kv[1][0][1300] = float("inf")                       # the first sequence's history, layer 1
+    dr.kv_update(to_device(up.features, cfg.dtype, dr.device), to_device(up.tokens, "i32", dr.device),
+                 to_device(up.positions, "i32", dr.device), to_device(up.dst_rows, "i32", dr.device), *kv)
+    last = kv[0][1][torch.from_numpy(up.dst_rows.astype(np.int64)).to(dr.device)].float().cpu().numpy()
+    dr.close()
+    assert np.isnan(last[:70]).all((1, 2)).all() and np.isfinite(last[70:]).all()
+
+
 def test_tiles_keep_nan_rows_apart():
     """A row whose token is outside the vocabulary is NaN, and with it the later
     rows of its sequence (they see its key), but no earlier row of its tile; a
