@@ -22,7 +22,7 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-def _update(cfg, w, up, split, max_prefix):
+def _update(cfg, w, up, split, max_prefix, chunk_rows=1024):
     """Caches (fp64 values) after one update; split 0 takes the tiles."""
     import torch
     from paper_2509_20416_amd import Drafter
@@ -34,21 +34,28 @@ def _update(cfg, w, up, split, max_prefix):
            for l in range(cfg.n_layers)] for n in "kv"]
     dr.kv_update(to_device(up.features, cfg.dtype, dr.device), to_device(up.tokens, "i32", dr.device),
                  to_device(up.positions, "i32", dr.device), to_device(up.dst_rows, "i32", dr.device),
-                 *kv)
+                 *kv, chunk_rows=chunk_rows)
     torch.cuda.synchronize()
     got = [t.double().cpu().numpy().reshape(up.cache_rows, -1) for side in kv for t in side]
     dr.close()
     return got
 
 
+# A tile is 64 (row, head) columns: 64, 32, 16 and 8 rows where a KV head has 1,
+# 2, 4 and 8 query heads.
 CASES = [  # rows per sequence, prefix per sequence
-    (SELF(C.SMALL_GQA_BF16), [64], [0]),                        # the fewest rows; 32-row tiles
+    (SELF(C.SMALL_GQA_BF16), [64], [0]),                        # the fewest rows; 16-row tiles
     (SELF(C.SMALL_GQA_BF16), [33, 1, 31, 65, 2], [0, 700, 31, 32, 1]),  # runs across tile edges
-    (SELF(C.SMALL_GQA8_BF16_D128), [17, 100], [0, 333]),        # 16-row tiles, head dim 128
-    (SELF(C.SMALL_MHA_BF16_D128), [129, 140], [5, 0]),          # 128-row tiles
-    (SELF(C.SMALL_GQA2_BF16), [70, 63], [0, 64]),               # 64-row tiles
+    (SELF(C.SMALL_GQA8_BF16_D128), [17, 100], [0, 333]),        # 8-row tiles, head dim 128
+    (SELF(C.SMALL_MHA_BF16_D128), [129, 140], [5, 0]),          # 64-row tiles
+    (SELF(C.SMALL_GQA2_BF16), [70, 63], [0, 64]),               # 32-row tiles
     (SELF(C.SMALL_GQA_BF16), [1] * 70, list(range(70))),        # every row a run of its own
-    (SELF(C.SMALL_GQA_BF16), [1100], [0]),                      # two chunks, more runs than one scan
+    (SELF(C.SMALL_GQA_BF16), [1100], [0]),                      # one run over two chunks
+    # one row short of a tile, a tile, one row more, one more than two tiles
+    (SELF(C.SMALL_GQA8_BF16_D128), [7, 8, 9, 17, 25], [40, 0, 3, 31, 32]),
+    (SELF(C.SMALL_GQA_BF16), [15, 16, 17, 33], [0, 33, 64, 5]),
+    (SELF(C.SMALL_GQA2_BF16), [31, 32, 33, 65], [9, 0, 65, 30]),
+    (SELF(C.SMALL_MHA_BF16_D128), [63, 64, 65, 129], [0, 31, 7, 100]),
 ]
 
 
@@ -60,6 +67,33 @@ def test_tiles_match_split_kernels(cfg, acc, plens):
     w = make_weights(cfg, 3)
     for i, (a, b) in enumerate(zip(_update(cfg, w, up, 0, cap), _update(cfg, w, up, 4, cap))):
         assert_rows_close(f"array {i}", a[up.dst_rows], b[up.dst_rows], TOL["bf16"])
+
+
+# More rows than one scan of the plan: the run that a round leaves off in goes on
+# in the next, at rows 1024 and 2048 that are inside a tile, and the tiles are
+# numbered on; more tiles than one round lists
+ROUNDS = [
+    (SELF(C.SMALL_GQA_BF16), [5, 2200, 3], [0, 7, 2]),
+    (SELF(C.SMALL_GQA8_BF16_D128), [1021, 1, 2, 1050], [0, 3, 9, 1]),
+    (SELF(C.SMALL_GQA2_BF16), [1, 2] * 760, [3, 0, 1, 6] * 380),
+]
+
+
+@pytest.mark.parametrize("cfg,acc,plens", ROUNDS, ids=[f"{c.name}-{len(a)}x{a[0]}" for c, a, _ in ROUNDS])
+def test_plan_of_several_rounds(cfg, acc, plens):
+    acc, plens = np.asarray(acc, np.int32), np.asarray(plens, np.int32)
+    cap = int((acc + plens).max())
+    up = make_update_rows(cfg, acc, plens, capacity=cap, seed=15)
+    assert len(up.tokens) > 2048
+    for row in (1023, 1024, 2047, len(up.tokens) - 1):
+        up.positions[row] = cap + row  # no such position: a tile of its own, NaN
+    w = make_weights(cfg, 3)
+    tiles, split = (_update(cfg, w, up, s, cap, chunk_rows=2600) for s in (0, 4))
+    for i, (a, b) in enumerate(zip(tiles, split)):
+        np.testing.assert_array_equal(np.isnan(a), np.isnan(b), err_msg=f"array {i}")
+        ok = up.dst_rows[~np.isnan(b[up.dst_rows]).any(1)]
+        assert len(ok) > 1000
+        assert_rows_close(f"array {i}", a[ok], b[ok], TOL["bf16"])
 
 
 # Histories that are cut into pieces over several workgroups (more than 32
