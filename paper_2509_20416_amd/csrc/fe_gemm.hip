@@ -142,8 +142,8 @@ template <class E> struct SlicedEpi<E, decltype((void)E::kSliced)> {
   static constexpr bool value = E::kSliced;
 };
 
-// Epilogues with a member bx: the workgroup's column block, where it is not
-// blockIdx.x (k_gemm_tile).
+// Epilogues with a member bx, the storing ones: the workgroup's column block,
+// where it is not blockIdx.x (k_gemm_tile), by which it picks embedding rows.
 template <class E, class = void> struct HasBlock { static constexpr bool value = false; };
 template <class E> struct HasBlock<E, decltype((void)std::declval<E>().bx)> {
   static constexpr bool value = true;
@@ -741,6 +741,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(const bf16_t *__restrict__ A,
           tile[mrow0 + i * 16 + 4 * g + v][((f - f0) * WN + wn) * 16 + r] = acc[i][f][v];
     __syncthreads();
     epi.finish(&tile[0][0], LDT, Mb, c0 + f0 * WN * 16, 16 * WN * min(FP, NTW - f0), typename Epi::Pre{});
+    if constexpr (HasBlock<Epi>::value) epi.embed = nullptr;  // its rows are copied by the first pass
   }
 }
 

@@ -147,11 +147,13 @@ Layout layout_of(const fe_config &c) {
 // one K/V launch over all layers), the rows' sums of squares for the fused
 // norm of chunks up to kFusedRows rows, and the split-K slices of a chunk's
 // GEMMs.  bf16 chunks above kFusedRows rows run the fusion and input FCs over
-// 2-D tiles with a pass over the rows after each; a d that is no multiple of
-// the tiles' 64-wide K chunk, and the self context, whose layers then run as
-// the pass's launches, do so only from kTiledRows rows, where one tiled launch
-// takes more rows than those (8B shapes, 147 rows: 115 us on tiles, 135 with
-// the pass's launches).
+// 2-D tiles with a pass over the rows after each (8B shapes, 147 rows: 115 us on
+// tiles, 135 with the pass's launches).  A d that is no multiple of the tiles'
+// 64-wide K chunk, and the self context, whose layers then run as the pass's
+// launches, do so only from kTiledRows rows, the most that those take at once:
+// its gate/up and Q/K/V have tiles for many rows only.  Three self-context
+// layers, pass's launches / tiles: 8B shapes 17 rows 295 / 411 us, 147 497 / 506,
+// 256 600 / 568; 2048 wide, 16 heads, 4 KV heads: 172 / 179, 305 / 250, 354 / 283.
 constexpr int kTiledRows = kGemmMaxRows + 1, kFusedRows = 16;
 // rows of a bf16 prefill step from which the attention runs over tiles of rows
 // (k_attn_tile).  The plan and the merge of cut tiles cost about 10 us a call
