@@ -438,7 +438,7 @@ hipError_t accept_greedy(int B, int N, int k, const int32_t *tokens, const int32
 // issues per id: a row pass tests a lane's four ids against one mask word and
 // adds the unmapped ones only (Z adds the gathered mapped values), a rejection
 // rewrites nothing (8 sequences at the 8B vocabularies: 99 us with a sum, a
-// mask test and a last-id update per id and a rewritten residual, 70 so).
+// mask test and a last-id update per id and a rewritten residual, 67 so).
 // Every decision is taken on block-reduced values, so control flow is
 // uniform across the workgroup.
 // ---------------------------------------------------------------------------
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
     // by the wave that holds the rejected id (s_qw: the waves' sums), since
     // 1 - (the rejected share) is all rounding once the rejected children hold
     // nearly all of q (a top logit 17 above the rest).
-    float C = 0.f;
+    float C = 0.f, unmapped = 0.f;
     bool took = false, cut = false;
     for (int j = 0; j < k; ++j) {
       const int rho = s_ord[j];
@@ -825,27 +825,31 @@ __global__ __launch_bounds__(kAccThreads) void k_accept_sample(
       }
       // r <- (r - Z q_i)^+, and x leaves q.  A rejected x had r(x) / Z < q_i(x),
       // so its r is 0 from here on: its weight becomes infinite.
-      C += Z / Qw;
+      if (!cut)
+#pragma unroll
+        for (int w = 0; w < kAccWaves; ++w) unmapped += s_cn[w];  // p at the ids q does not reach
       cut = true;
+      C += Z / Qw;
+      float r = 0.f;
       if (wave == ((vd % kAccThreads) >> 6)) {
         float q = 0.f;
 #pragma unroll
         for (int jj = 0; jj < kZ; ++jj) {
-          if (tid + jj * kAccThreads == vd) zr[jj] = INFINITY;
+          const int v = tid + jj * kAccThreads;
+          if (v == vd) zr[jj] = INFINITY;
           q += zr[jj] < INFINITY ? zr[jj] : 0.f;
+          r += v < V ? fmaxf(s_rd[v] - C * zr[jj], 0.f) : 0.f;
         }
         q = group_sum<64>(q);
         if (lane == 0) s_qw[wave] = q;
-      }
-      float r = 0.f;
+      } else {
 #pragma unroll
-      for (int jj = 0; jj < kZ; ++jj) {
-        const int v = tid + jj * kAccThreads;
-        r += v < V ? fmaxf(s_rd[v] - C * zr[jj], 0.f) : 0.f;
+        for (int jj = 0; jj < kZ; ++jj) {
+          const int v = tid + jj * kAccThreads;
+          r += v < V ? fmaxf(s_rd[v] - C * zr[jj], 0.f) : 0.f;
+        }
       }
-      Z = acc_sum<false, true>(r, red, s_qw, &Qw);
-#pragma unroll
-      for (int w = 0; w < kAccWaves; ++w) Z += s_cn[w];  // the ids q does not reach
+      Z = unmapped + acc_sum<false, true>(r, red, s_qw, &Qw);
       // The untested children hold next to nothing of q: testing them would
       // only divide by that.  The draw from the residual is as exact.
       if (!(Qw > kAccMinWeight)) break;
