@@ -753,7 +753,7 @@ constexpr int kMaxSlices = 8;
 // rounds of workgroups cost least; K may be split over as many workgroups per
 // tile (at most kMaxSlices) as slices of its padded columns fit in `floats`,
 // where the caller sums the slices, which costs a write and a read of each.
-// The first shapes are for up to 256 rows only: one row block holds them all,
+// The first shapes are for up to 160 rows only: one row block holds them all,
 // so that every weight is read once, and a narrow one spreads few columns over
 // the chip.  Measured with one workgroup per CU: 147 rows x 4096 columns,
 // K 12288 in 8 slices 28 us with 160 x 128 against 32 with 256 x 128; the K/V
@@ -763,7 +763,7 @@ enum TileShape {
   kTile64x64 = 0, kTile96x64, kTile128x64, kTile160x64, kTile64x128, kTile96x128, kTile160x128,
   kTile128x128, kTile128x192, kTile128x256, kTile256x224, kTile256x256, kTileShapes
 };
-constexpr int kTileFirstMany = kTile128x128;  // the shapes before serve up to 256 rows
+constexpr int kTileFirstMany = kTile128x128;  // the shapes before serve as many rows as they are high
 struct TilePick {
   int shape, ks;
 };
@@ -806,7 +806,7 @@ static TilePick pick_tile(int M, int ncols, int K, int groups, size_t floats) {
 // tiles take a three-stage ring when the grid is about one workgroup per CU
 // (96 KB of LDS), else two stages, which lets two workgroups share a CU (1024
 // rows x 6144 columns, K 4096: 75 us with three stages, 59 with two).  FEW: the
-// shapes of up to 256 rows are built for this epilogue.
+// shapes of up to 160 rows are built for this epilogue.
 template <class Epi, bool SPLIT, bool FEW>
 static hipError_t launch_tile(const TilePick &p, const bf16_t *A, int lda, int M, int K, const Epi &e,
                               int groups, float *sp, int ldp, hipStream_t s) {

@@ -157,7 +157,8 @@ template <> struct Elt<float> {
 constexpr int kMaxLayers = 16;
 // Prefix keys per attention workgroup (4 waves of 32 keys).
 constexpr int kAttnChunk = 64;
-// Tile candidates the top-k merge holds in registers: 256 threads x 32.
+// Largest number of LM-head tiles times k: the top-k merge holds a row's tiles
+// in registers, 32 per thread of 256 at most.
 constexpr int kMergeMaxCand = 256 * 32;
 // Largest M (rows) one GEMM launch handles; larger M is split on the host.
 constexpr int kGemmMaxRows = 256;
