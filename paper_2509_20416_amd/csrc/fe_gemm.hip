@@ -1619,7 +1619,8 @@ template <typename T> struct EpiLm {
     const int l16 = lane & 15, base = lane & 48;
     const int nseg = span >> 6, items = M * nseg, ntile = (nvcols + 63) >> 6;
     const bool vec = aligned16(a.logits), gen = a.draws.so != nullptr, on = a.draws.on();
-    const uint32_t nan_key = M <= 16 ? 1u : 0u, ninf_key = M <= 16 ? 0x007fffffu : 0u;
+    const uint32_t nan_key = M <= 16 ? 1u : 0u;
+    const uint32_t none = M <= 16 ? 0u : 0x007fffffu;  // a winner up to this key (-inf) is no candidate
     const uint64_t seed = gen ? a.draws.so[0] : 0, offset = gen ? a.draws.so[1] : 0;
     for (int i0 = 4 * U * wave; i0 < items; i0 += 4 * U * nw) {
       float v[U][4], mx[U], se[U];
@@ -1673,8 +1674,7 @@ template <typename T> struct EpiLm {
         for (int q = 0; q < 4; ++q) {
           const float kf = on ? v[u][q] - logf(-logf(n[q])) : v[u][q];
           const uint32_t w = __float_as_uint(kf);
-          const uint32_t low = kf != kf ? nan_key : ninf_key;
-          key[u][q] = !ok ? 0u : !(kf > -INFINITY) ? low : (w & 0x80000000u) ? ~w : (w | 0x80000000u);
+          key[u][q] = !ok ? 0u : kf != kf ? nan_key : (w & 0x80000000u) ? ~w : (w | 0x80000000u);
         }
       }
       uint32_t got[U];  // lane r: the r-th best key, its column and its z / T
@@ -1718,7 +1718,7 @@ template <typename T> struct EpiLm {
           a.part_sum[pb[u]] = se[u];
         }
         if (l16 < a.topk) {
-          const uint32_t g = got[u];
+          const uint32_t g = got[u] > none ? got[u] : 0u;
           const float val = g == 1u ? __int_as_float(0x7fc00000)
                                     : __uint_as_float((g & 0x80000000u) ? (g & 0x7fffffffu) : ~g);
           a.cand_val[pb[u] * kMaxTopk + l16] = g ? val : -INFINITY;
